@@ -72,8 +72,7 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
         off += align256(bytes);
         return o;
     };
-    for (int f = 0; f < NFIELD; ++f) L->field[f] = take(N * es);
-    for (int m = 0; m < 4; ++m) L->map[m] = take(N * es);
+    for (int f = 0; f < NFIELD + 4; ++f) L->vol[f] = take(N * es);
     const int P = g.npml;
     const size_t W = P > 0 ? 2 * (size_t)(P + 7) : 0;
     const size_t ns[3] = {W * g.ny * g.nz, (size_t)g.nx * W * g.nz, (size_t)g.nx * g.ny * W};
@@ -81,14 +80,11 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
     for (int a = 0; a < 3; ++a)
         for (int q = 0; q < 6; ++q) L->mem[a][q] = P > 0 ? take(ns[a] * es) : 0;
     for (int a = 0; a < 3; ++a)
-        for (int h = 0; h < 2; ++h) {
-            L->pa[a][h] = P > 0 ? take(n[a] * es) : 0;
-            L->pb[a][h] = P > 0 ? take(n[a] * es) : 0;
-        }
+        for (int q = 0; q < 4; ++q) L->coef[a][q] = take(n[a] * es);
     const size_t E = 8 * (size_t)std::max(nrec, 1);
     L->rec_idx = take(E * 8);
     L->rec_w = take(E * 8);
-    L->rec_fl = take(E);
+    for (size_t &o : L->rec_fl) o = take(E);
     L->csr_pt = take(E * 8);
     L->csr_ptc = take(E * 3 * 4);
     L->csr_row = take((E + 1) * 4);
@@ -98,14 +94,15 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
     L->counter = take(256);
     {
         const Tiles t = make_tiles(g.nx, g.ny, g.nz);
-        L->csr_tslot = take((size_t)t.ntiles * 4);
-        L->csr_loff = take(std::min((size_t)t.ntiles, E) * (kTileX * kTileY + 1) * 4);
-        L->csr_tpts = take(E * 4);
-        L->tile_order = take((size_t)8 * t.per * sizeof(int));
+        // increments: the planes of a sub-tile's piece with points, at most every plane there is
+        const size_t planes = std::min(E * t.longest(), (size_t)4 * t.ntx * t.nty * g.nz);
+        for (size_t &o : L->csr_pos) o = take(E * 4);
+        for (size_t &o : L->inc) o = take(planes * kWaveX * kWaveY * es);
+        for (size_t &o : L->tile_order) o = take((size_t)8 * t.cap * sizeof(BlockEnt<double>));
         L->tile_flags = take(2 * (size_t)t.ntiles);
         L->tile_media = take((size_t)4 * t.ntiles * es);
         L->tile_lanes = take((size_t)2 * kTileY * t.ntiles * 8);
-        L->energy = take((size_t)(kTileX * kTileY + 2) * 8 * t.per * sizeof(double));
+        L->energy = take(((size_t)(4 + 1) * 8 * t.cap + (size_t)8 * t.cap / 64 + 1) * sizeof(double));
         const int nm = g.relax.nmech;
         L->relax_map = nm > 0 ? take(N * es) : 0;
         L->relax_flag = nm > 0 ? take((size_t)t.ntiles) : 0;
@@ -121,78 +118,231 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
     return true;
 }
 
-// Tiles of kTileX x kTileY columns by chunks of chunk_planes() planes.  Chunks of kZChunk
-// planes where the grid has enough columns (measured at 384^3 with the fluid update and its
-// pipelined loops: 6 planes beat 4 by 1.2%, 8 by 0.5% and 12 by 1.7%; short blocks keep the
-// XCDs evenly loaded, long ones re-read fewer halo planes).  A small grid takes shorter
-// chunks until it has kMinTiles tiles (16 blocks per compute unit): at 96^3 chunks of 2
-// planes make the adjoint passes 1.5x and the forward passes 1.15x faster than chunks of 6
-// (768 blocks, under three per compute unit), at 128^3 1.2x and 1.1x.
-// The grid has 8 * per blocks; tile_order() says which tile each block processes.
+// Tiles of kTileX x kTileY columns by chunks of chunk_planes() planes: kZChunk where that makes
+// kMinTiles tiles, else fewer, down to two.  The chunk decides which cells next to a solid run the
+// general update, whose sums round differently from the fluid update's.  How many planes a block
+// updates is another matter (block_planes): the blocks of block_list() cover any run of planes
+// over which a tile column's chunks ask for the same update.
 constexpr int kZChunk = 6;
 constexpr long long kMinTiles = 4096;
+constexpr int kMaxTiles = (1 << 24) - 1;   // (arrays below 4 GiB keep under it)
 int chunk_planes(int nx, int ny, int nz) {
     const long long cols = (long long)((nx + kTileX - 1) / kTileX) * ((ny + kTileY - 1) / kTileY);
     int zc = kZChunk;
     while (zc > 2 && cols * ((nz + zc - 1) / zc) < kMinTiles) --zc;
     return std::min(zc, nz);
 }
+// Planes per block.  A long column of planes reads fewer halo planes, a short one gives more
+// wavefronts and a shorter chain of planes per wavefront.  Measured with chunks and blocks of the
+// same depth (skull medium, forward / adjoint us per step, 2, 3, 4 and 6 planes): 64^3 14.8/16.3,
+// 15.4/16.0, 16.5/16.8, 19.5/19.1; 96^3 27.7/31.4, 25.8/29.7, 27.6/29.8, 26.7/32.7; 128^3
+// 43.0/49.6, 41.9/46.4, 43.1/46.7, 45.2/48.7; 192^3 120/140, 115/129, 115/126, 118/126; 256^3
+// 285/336, 274/304, 277/295, 281/295; 384^3 800/935, 795/854, 798/831, 804/831.  So 4 planes, 3
+// where that leaves under 4096 blocks of a tile (128^3 and less), and 2 where even 3 leave under
+// 1024 (64^3).
+constexpr int kZBlock = 4;
+constexpr long long kFewTiles = 4096, kVeryFewTiles = 1024;
+int block_planes(int nx, int ny, int nz) {
+    const long long cols = (long long)((nx + kTileX - 1) / kTileX) * ((ny + kTileY - 1) / kTileY);
+    int zb = kZBlock;
+    if (cols * ((nz + zb - 1) / zb) < kFewTiles) --zb;
+    if (zb < kZBlock && cols * ((nz + zb - 1) / zb) < kVeryFewTiles) --zb;
+    return zb;
+}
 Tiles make_tiles(int nx, int ny, int nz) {
     Tiles t;
     t.ntx = (nx + kTileX - 1) / kTileX;
     t.nty = (ny + kTileY - 1) / kTileY;
     t.zc = chunk_planes(nx, ny, nz);
+    t.zb = block_planes(nx, ny, nz);
+    t.nz = nz;
     t.nzc = (nz + t.zc - 1) / t.zc;
     t.ntiles = t.ntx * t.nty * t.nzc;
     t.order = nullptr;
-    t.lanes = nullptr;
-    t.per = 0;
-    std::vector<int> cnt(8, 0);
-    for (int q = 0; q < t.ntiles; ++q) ++cnt[tile_xcd(t, q)];
-    for (int x = 0; x < 8; ++x) t.per = std::max(t.per, cnt[x]);
+    t.per = t.cap = 0;
+    // an XCD's entries at most: four per piece, the pieces of a tile column at least two planes
+    // apart but for a last one
+    long long cnt[8] = {}, all = 0;
+    for (int by = 0; by < t.nty; ++by)
+        for (int z0 = 0, z1 = 0; z0 < nz; z0 = z1) {
+            for (z1 = z0 + 1; z1 < nz && z1 * 8 / nz == z0 * 8 / nz; ++z1) {}
+            const int n = 4 * t.ntx * ((z1 - z0 + 1) / 2 + 1);
+            cnt[piece_xcd(t, by, z0, 0)] += n;
+            all += n;
+        }
+    t.cap = (int)*std::max_element(cnt, cnt + 8);
+    if (!t.bands()) t.cap = (int)((all + 7) / 8 + 4 * t.run());
     return t;
 }
 
-// XCD of a tile.  With at least eight tile rows and eight z chunks, the rows and chunks are
-// cut into eight bands each and region (y band, z band) goes to XCD (y band + z band) mod 8:
-// a Latin square, so every XCD holds one region of every y band and of every z band (the
-// same share of the C-PML layers of y and z; every region spans the x extent) and a
-// region's tiles share one L2.  Smaller grids deal runs of about ntiles / 512 tiles in
-// z-major order round-robin.
-int tile_xcd(const Tiles &t, int q) {
-    const int bx = q % t.ntx, r = q / t.ntx, by = r % t.nty, bz = r / t.nty;
-    (void)bx;
-    if (t.nty >= 8 && t.nzc >= 8) return (by * 8 / t.nty + bz * 8 / t.nzc) % 8;
-    const int run = std::max(1, (t.ntiles + 511) / 512);
-    return (q / run) % 8;
+// XCD of a piece of a tile column.  With at least eight tile rows and eight pieces along z, the
+// rows and the planes are cut into eight bands each and region (y band, z band) goes to XCD
+// (y band + z band) mod 8: a Latin square, so every XCD holds one region of every y band and of
+// every z band (the same share of the C-PML layers of y and z; every region spans the x extent)
+// and a region's neighbouring tiles share one L2.  Smaller grids deal runs of pieces (index: the
+// piece's number in z-major order) round-robin.
+int piece_xcd(const Tiles &t, int by, int z, long long index) {
+    if (t.bands()) return (by * 8 / t.nty + z * 8 / t.nz) % 8;
+    return (int)(index / t.run() % 8);
 }
 
-int tile_edges(const Tiles &t, const unsigned char *fast, int q) {
+unsigned tile_edges(const Tiles &t, const unsigned char *fast, int q) {
     if (!fast || !fast[q]) return 0;
     const int b[2] = {(q / t.ntx) % t.nty, q / t.ntx / t.nty};
     const int nb[2] = {t.nty, t.nzc};
     const int step[2] = {t.ntx, t.ntx * t.nty};
-    int edges = 0;
+    unsigned edges = 0;
     for (int a = 0; a < 2; ++a) {   // y, z
-        if (b[a] > 0 && !fast[q - step[a]]) edges |= 1 << (kEdgeShift + 2 * a);
-        if (b[a] + 1 < nb[a] && !fast[q + step[a]]) edges |= 1 << (kEdgeShift + 2 * a + 1);
+        if (b[a] > 0 && !fast[q - step[a]]) edges |= 1u << (2 * a);
+        if (b[a] + 1 < nb[a] && !fast[q + step[a]]) edges |= 1u << (2 * a + 1);
     }
     return edges;
 }
 
-std::vector<int> tile_order(const Tiles &t, const unsigned char *fast, const unsigned char *uni,
-                            const unsigned char *cols) {
-    std::vector<int> order((size_t)8 * t.per, -1);
-    std::vector<int> fill(8, 0);
-    // tiles of an XCD in z-major order: a region's tiles are consecutive
-    for (int q = 0; q < t.ntiles; ++q) {
-        const int x = tile_xcd(t, q);
-        const bool f = fast && fast[q];
-        const int flags = f ? kFastTile | tile_edges(t, fast, q) | (uni && uni[q] ? kUniformTile : 0)
-                            : (fast && cols && cols[q] ? kColumnTile : 0);
-        order[(size_t)fill[x]++ * 8 + x] = q | flags;
+// Do chunks q and q + step of a tile column (one above the other) ask for the same update?
+template <typename T>
+bool same_update(const Tiles &t, const unsigned char *fast, const unsigned char *uni, const unsigned long long *lanes,
+                 const T *med, int q) {
+    const int r = q + t.ntx * t.nty;
+    if (!fast) return true;
+    const bool med_same = med[4 * (size_t)q] == med[4 * (size_t)r] && med[4 * (size_t)q + 1] == med[4 * (size_t)r + 1] &&
+                          med[4 * (size_t)q + 2] == med[4 * (size_t)r + 2];
+    if (fast[q] != fast[r]) return false;
+    if (fast[q])
+        return uni[q] == uni[r] && (!uni[q] || med_same) && (tile_edges(t, fast, q) & 3) == (tile_edges(t, fast, r) & 3);
+    const unsigned long long *fq = lanes + (size_t)kTileY * q, *fr = lanes + (size_t)kTileY * r;
+    const size_t un = (size_t)kTileY * t.ntiles;   // the uniform columns' masks
+    unsigned long long any = 0;
+    for (int w = 0; w < kTileY; ++w) {
+        if (fq[w] != fr[w] || fq[un + w] != fr[un + w]) return false;
+        any |= fq[un + w];
     }
-    return order;
+    return !any || med_same;
+}
+
+template <typename T>
+BlockList<T> block_list(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned char *uni,
+                        const unsigned long long *lanes, const T *med, const std::vector<int> &points) {
+    // room for cap entries per XCD (an entry costs its 64 bytes only once it is written)
+    BlockList<T> out;
+    out.entries.reset(new BlockEnt<T>[8 * (size_t)t.cap]);
+    BlockEnt<T> *order = out.entries.get();
+    size_t count[8] = {};
+    // per tile column: its run of chunks that ask for the same update, and the next plane to cover
+    struct Run {
+        int z0, z1, next;
+    };
+    std::vector<Run> runs((size_t)t.ntx * t.nty, Run{0, 0, 0});
+    const int step = t.ntx * t.nty;
+    // with scatter points: the pieces (entries at first, first + 8, ..., n of them; their sub-tiles
+    // with points; the first one's first increment plane), and per column and plane, 1 + the number
+    // of the piece that begins there
+    struct Piece {
+        size_t first;
+        int n, z0, z1;
+        unsigned with;
+        int slot;
+    };
+    std::vector<Piece> piece;
+    std::vector<int> begins(points.empty() ? 0 : (size_t)step * t.nz, 0);
+    long long pieces = 0;
+    for (int z = 0; z < t.nz; ++z)
+        for (int by = 0; by < t.nty; ++by)
+            for (int bx = 0; bx < t.ntx; ++bx) {
+                Run &run = runs[by * t.ntx + bx];
+                if (run.next != z) continue;
+                const int bz = z / t.zc, q = bz * step + by * t.ntx + bx;
+                if (run.z1 == z) {   // the next run (runs end with a chunk)
+                    int e = q;
+                    while (e + step < t.ntiles && same_update(t, fast, uni, lanes, med, e)) e += step;
+                    run = {z, std::min((e / step + 1) * t.zc, t.nz), z};
+                }
+                // a piece of it: to the next multiple of zb, where all columns are cut, if that
+                // leaves neither piece under the shortest (the last of a long run has two planes at
+                // least: a deep one would come last on its XCD and the others wait for it)
+                int cut = (z + t.shortest() + t.zb - 1) / t.zb * t.zb;
+                if (run.z1 - cut < (z == run.z0 ? t.shortest() : 2)) cut = run.z1;
+                run.next = cut;
+                const int x = piece_xcd(t, by, z, pieces++);
+                const size_t first = count[x];
+                BlockEnt<T> e = {bx, by, z, cut, 0, -1, {}, {}, med[4 * (size_t)q], med[4 * (size_t)q + 1], med[4 * (size_t)q + 2]};
+                unsigned in = 0, fl = 0, un = 0;   // sub-tiles with columns in the grid; those all fluid; those all uniform
+                unsigned fluid[4][kWaveY] = {}, uniform[4][kWaveY] = {};
+                for (int s = 0; s < 4; ++s) {
+                    const int x0 = bx * kTileX + (s & 1) * kWaveX, y0 = by * kTileY + (s >> 1) * kWaveY;
+                    if (x0 >= nx || y0 >= ny) continue;
+                    in |= 1u << s;
+                    if (!fast || fast[q]) continue;
+                    const unsigned valid = nx - x0 >= kWaveX ? ~0u : (1u << (nx - x0)) - 1;
+                    bool all = true, same = true;
+                    for (int r = 0; r < kWaveY && y0 + r < ny; ++r) {
+                        const size_t row = (size_t)kTileY * q + (s >> 1) * kWaveY + r;
+                        fluid[s][r] = (unsigned)(lanes[row] >> ((s & 1) * kWaveX)) & valid;
+                        uniform[s][r] = (unsigned)(lanes[(size_t)kTileY * t.ntiles + row] >> ((s & 1) * kWaveX)) & valid;
+                        all = all && fluid[s][r] == valid;
+                        same = same && uniform[s][r] == valid;
+                    }
+                    if (all) fl |= 1u << s;
+                    if (all && same) un |= 1u << s;
+                }
+                auto put = [&](unsigned flags) {
+                    e.flags = flags | (count[x] == first ? kBlkFirst : 0u);
+                    order[8 * count[x]++ + x] = e;
+                };
+                if (fast && fast[q]) {
+                    unsigned edges = tile_edges(t, fast, q) & 3u;
+                    if (e.z0 == run.z0) edges |= tile_edges(t, fast, q) & 4u;
+                    if (e.z1 == run.z1) edges |= tile_edges(t, fast, q + ((run.z1 - 1) / t.zc - bz) * step) & 8u;
+                    put(kBlkFast | in << kBlkMaskShift | (uni[q] ? in << kBlkUniShift : 0u) | edges << kBlkEdgeShift);
+                } else {
+                    for (int s = 0; s < 4; ++s) {
+                        if (!((in & ~fl) >> s & 1u)) continue;
+                        for (int r = 0; r < kWaveY; ++r) {
+                            e.fluid[r] = fluid[s][r];
+                            e.uniform[r] = uniform[s][r];
+                        }
+                        put(kBlkGen | (unsigned)s << kBlkSubShift);
+                    }
+                    if (fl) put(kBlkKeep | fl << kBlkMaskShift | un << kBlkUniShift);
+                }
+                if (points.empty()) continue;
+                piece.push_back({8 * first + x, (int)(count[x] - first), z, cut, 0u, 0});
+                begins[(size_t)z * step + by * t.ntx + bx] = (int)piece.size();
+            }
+    // increments: the planes of every sub-tile's piece with points, one after the other; a point's
+    // element there (plane, then lane)
+    const size_t np = points.size() / 3;
+    std::vector<int> of(np);
+    for (size_t p = 0; p < np; ++p) {
+        const int i = points[3 * p], j = points[3 * p + 1];
+        size_t at = (size_t)points[3 * p + 2] * step + j / kTileY * t.ntx + i / kTileX;
+        while (!begins[at]) at -= step;
+        of[p] = begins[at] - 1;
+        piece[of[p]].with |= 1u << (2 * (j % kTileY / kWaveY) + i % kTileX / kWaveX);
+    }
+    for (Piece &p : piece) {
+        if (!p.with) continue;
+        p.slot = (int)out.planes;
+        out.planes += __builtin_popcount(p.with) * (p.z1 - p.z0);
+        for (int n = 0; n < p.n; ++n) {
+            order[p.first + 8 * (size_t)n].slot = p.slot;
+            order[p.first + 8 * (size_t)n].flags |= p.with << kBlkIncShift;
+        }
+    }
+    out.pos.resize(np);
+    for (size_t q = 0; q < np; ++q) {
+        const int i = points[3 * q], j = points[3 * q + 1], k = points[3 * q + 2];
+        const Piece &p = piece[of[q]];
+        const int sub = 2 * (j % kTileY / kWaveY) + i % kTileX / kWaveX;
+        const int plane = p.slot + __builtin_popcount(p.with & ((1u << sub) - 1u)) * (p.z1 - p.z0) + k - p.z0;
+        out.pos[q] = (plane * kWaveY + j % kWaveY) * kWaveX + i % kWaveX;
+    }
+    size_t per = 0;
+    for (int x = 0; x < 8; ++x) per = std::max(per, count[x]);
+    out.per = (int)per;
+    for (int x = 0; x < 8; ++x)
+        for (size_t e = count[x]; e < per; ++e) order[8 * e + x] = BlockEnt<T>{};
+    return out;
 }
 
 }  // namespace el
@@ -250,8 +400,8 @@ el_status el_grid_check(const el_grid *g, const double *rec, int32_t nrec) {
         const int zc = chunk_planes(g->nx, g->ny, g->nz);
         const long long tiles = (long long)((g->nx + kTileX - 1) / kTileX) * ((g->ny + kTileY - 1) / kTileY) *
                                 ((g->nz + zc - 1) / zc);
-        if (tiles > kTileMask)
-            return fail(EL_EINVAL, "grid %dx%dx%d: %lld stencil tiles, at most %d", g->nx, g->ny, g->nz, tiles, kTileMask);
+        if (tiles > kMaxTiles)
+            return fail(EL_EINVAL, "grid %dx%dx%d: %lld stencil tiles, at most %d", g->nx, g->ny, g->nz, tiles, kMaxTiles);
     }
     {
         const el_relaxation &rx = g->relax;
@@ -323,29 +473,25 @@ void bind(Dev<T> &d, el_plan_ *p) {
     d.nx = g.nx;
     d.ny = g.ny;
     d.nz = g.nz;
-    d.px = v.px;
-    d.plane = v.plane;
+    d.P = g.npml > 0 ? g.npml : kNoPml;
     d.sy = (unsigned)(v.px * sizeof(T));
     d.sz = (unsigned)(v.plane * sizeof(T));
-    d.origin = (unsigned)(v.origin * sizeof(T));
     d.dt = T(g.dt);
     d.inv_dx = T(1.0 / g.dx);
-    for (int f = 0; f < NFIELD; ++f) d.f[f] = reinterpret_cast<T *>(ws + p->L.field[f]);
-    d.lam = reinterpret_cast<T *>(ws + p->L.map[0]);
-    d.mu = reinterpret_cast<T *>(ws + p->L.map[1]);
-    d.rho = reinterpret_cast<T *>(ws + p->L.map[2]);
-    d.alpha = reinterpret_cast<T *>(ws + p->L.map[3]);
-    d.med = reinterpret_cast<T *>(ws + p->L.tile_media);
-    d.P = g.npml;
+    d.ws = ws;
+    auto u256 = [](size_t off) { return (unsigned)(off >> 8); };
+    const Layout &L = p->L;
+    d.vstr = u256(L.vol[1] - L.vol[0]);
+    d.incoff = u256(L.inc[1]);
     const int n[3] = {g.nx, g.ny, g.nz};
-    for (int a = 0; a < 3; ++a) d.hi[a] = n[a] - 1 - g.npml;
-    d.W = g.npml > 0 ? 2 * (g.npml + 7) : 0;
     for (int a = 0; a < 3; ++a) {
-        for (int h = 0; h < 2; ++h) {
-            d.pa[a][h] = g.npml > 0 ? reinterpret_cast<T *>(ws + p->L.pa[a][h]) : nullptr;
-            d.pb[a][h] = g.npml > 0 ? reinterpret_cast<T *>(ws + p->L.pb[a][h]) : nullptr;
-        }
-        for (int q = 0; q < 6; ++q) d.mem[a][q] = g.npml > 0 ? reinterpret_cast<T *>(ws + p->L.mem[a][q]) : nullptr;
+        const bool single = n[a] <= 2 * g.npml + 9;   // (npml = 0: not used)
+        d.high[a] = single ? 2 : (g.npml + 7) - (n[a] - 1 - g.npml - 4);
+        if (a == 0) d.xw = single ? d.W() : g.npml + 7;
+        d.moff[a] = u256(L.mem[a][0]);
+        d.mstr[a] = u256(L.mem[a][1] - L.mem[a][0]);
+        d.coff[a] = u256(L.coef[a][0]);
+        d.cstr[a] = u256(L.coef[a][1] - L.coef[a][0]);
     }
 }
 
@@ -373,21 +519,31 @@ void bind_relax(Relax<T> &r, el_plan_ *p) {
 template <typename T>
 el_status upload_pml(el_plan_ *p, Dev<T> &d, hipStream_t s) {
     const el_grid &g = p->g;
-    if (g.npml <= 0) return EL_OK;
     const double R = g.pml_R > 0 ? g.pml_R : 1e-3;
     const double npow = g.pml_npower > 0 ? g.pml_npower : 2.0;
     const double f0 = g.pml_f0 > 0 ? g.pml_f0 : 1500.0 / (8.0 * g.dx);
-    const double d0 = -(npow + 1.0) * p->cmax * std::log(R) / (2.0 * g.npml * g.dx);
+    const double d0 = g.npml > 0 ? -(npow + 1.0) * p->cmax * std::log(R) / (2.0 * g.npml * g.dx) : 0.0;
     const int n[3] = {g.nx, g.ny, g.nz};
     std::vector<double> a, b;
     for (int ax = 0; ax < 3; ++ax)
         for (int h = 0; h < 2; ++h) {
-            pml_axis(g, n[ax], d0, f0, npow, h, a, b);
-            std::vector<T> at(a.begin(), a.end()), bt(b.begin(), b.end());
-            HIP_TRY(hipMemcpyAsync(const_cast<T *>(d.pa[ax][h]), at.data(), n[ax] * sizeof(T), hipMemcpyHostToDevice, s),
-                    "copy PML a");
-            HIP_TRY(hipMemcpyAsync(const_cast<T *>(d.pb[ax][h]), bt.data(), n[ax] * sizeof(T), hipMemcpyHostToDevice, s),
-                    "copy PML b");
+            if (g.npml > 0) {
+                pml_axis(g, n[ax], d0, f0, npow, h, a, b);
+            } else {
+                a.assign(n[ax], 0.0);
+                b.assign(n[ax], 1.0);
+            }
+            std::vector<T> at(a.begin(), a.end()), bt(b.begin(), b.end()), ab;
+            if (ax == 2) {
+                for (int k = 0; k < n[2]; ++k) {
+                    ab.push_back(at[k]);
+                    ab.push_back(bt[k]);
+                }
+                HIP_TRY(hipMemcpyAsync(d.zab(h), ab.data(), ab.size() * sizeof(T), hipMemcpyHostToDevice, s), "copy PML a, b");
+            } else {
+                HIP_TRY(hipMemcpyAsync(d.pa(ax, h), at.data(), n[ax] * sizeof(T), hipMemcpyHostToDevice, s), "copy PML a");
+                HIP_TRY(hipMemcpyAsync(d.pb(ax, h), bt.data(), n[ax] * sizeof(T), hipMemcpyHostToDevice, s), "copy PML b");
+            }
             HIP_TRY(hipStreamSynchronize(s), "PML upload");
         }
     return EL_OK;
@@ -443,55 +599,18 @@ el_status upload_receivers(el_plan_ *p, const double *rec, hipStream_t s) {
         ew.push_back(w[o]);
     }
     row.push_back((int)order.size());
-    // the points of each stencil tile and column (the adjoint stress launch adds Theta^T y at
-    // the cells its lanes own): sorted by (tile, column key), a slot per tile with points
-    const Tiles &tt = p->tiles;
-    constexpr int kKeys = kTileX * kTileY;
-    std::vector<long long> tkey(pt.size());
-    std::vector<int> tpts(pt.size()), tslot(tt.ntiles, -1), loff;
-    for (size_t q = 0; q < pt.size(); ++q) {
-        const int i = ptc[3 * q], j = ptc[3 * q + 1], k = ptc[3 * q + 2];
-        const long long t = ((long long)(k / tt.zc) * tt.nty + j / kTileY) * tt.ntx + i / kTileX;
-        tkey[q] = t * kKeys + (i % kTileX) + kTileX * (j % kTileY);
-        tpts[q] = (int)q;
-    }
-    std::stable_sort(tpts.begin(), tpts.end(), [&](int a, int b) { return tkey[a] < tkey[b]; });
-    for (size_t e = 0; e < tpts.size();) {
-        const int t = (int)(tkey[tpts[e]] / kKeys);
-        const int slot = (int)(loff.size() / (kKeys + 1));
-        tslot[t] = slot;
-        loff.resize(loff.size() + kKeys + 1);
-        int *lo = loff.data() + (size_t)slot * (kKeys + 1);
-        size_t f = e;
-        for (int key = 0; key <= kKeys; ++key) {
-            while (f < tpts.size() && tkey[tpts[f]] < (long long)t * kKeys + key) ++f;
-            lo[key] = (int)f;
-        }
-        while (f < tpts.size() && tkey[tpts[f]] / kKeys == t) ++f;
-        e = f;
-    }
     char *ws = p->ws;
     Rec &r = p->rec;
     r.nrec = L;
     r.idx = reinterpret_cast<long long *>(ws + p->L.rec_idx);
     r.w = reinterpret_cast<double *>(ws + p->L.rec_w);
-    r.fl = reinterpret_cast<unsigned char *>(ws + p->L.rec_fl);
     r.npts = (int)pt.size();
     r.pt = reinterpret_cast<long long *>(ws + p->L.csr_pt);
     r.ptc = reinterpret_cast<int *>(ws + p->L.csr_ptc);
     r.row = reinterpret_cast<int *>(ws + p->L.csr_row);
     r.ent_rec = reinterpret_cast<int *>(ws + p->L.csr_rec);
     r.ent_w = reinterpret_cast<double *>(ws + p->L.csr_w);
-    r.tslot = reinterpret_cast<int *>(ws + p->L.csr_tslot);
-    r.loff = reinterpret_cast<int *>(ws + p->L.csr_loff);
-    r.tpts = reinterpret_cast<int *>(ws + p->L.csr_tpts);
-    HIP_TRY(hipMemcpyAsync((void *)r.tslot, tslot.data(), tslot.size() * 4, hipMemcpyHostToDevice, s),
-            "copy receivers");
     if (L > 0) {
-        HIP_TRY(hipMemcpyAsync((void *)r.loff, loff.data(), loff.size() * 4, hipMemcpyHostToDevice, s),
-                "copy receivers");
-        HIP_TRY(hipMemcpyAsync((void *)r.tpts, tpts.data(), tpts.size() * 4, hipMemcpyHostToDevice, s),
-                "copy receivers");
         HIP_TRY(hipMemcpyAsync((void *)r.idx, idx.data(), idx.size() * 8, hipMemcpyHostToDevice, s), "copy receivers");
         HIP_TRY(hipMemcpyAsync((void *)r.w, w.data(), w.size() * 8, hipMemcpyHostToDevice, s), "copy receivers");
         HIP_TRY(hipMemcpyAsync((void *)r.pt, pt.data(), pt.size() * 8, hipMemcpyHostToDevice, s), "copy receivers");
@@ -502,23 +621,44 @@ el_status upload_receivers(el_plan_ *p, const double *rec, hipStream_t s) {
         HIP_TRY(hipMemcpyAsync((void *)r.ent_w, ew.data(), ew.size() * 8, hipMemcpyHostToDevice, s), "copy receivers");
     }
     HIP_TRY(hipStreamSynchronize(s), "receiver upload");
+    p->points = std::move(ptc);
     return EL_OK;
 }
 
-// Upload the tile order table and the receiver corners' fluid flags, both with the fluid
-// tiles when the fluid update is enabled and without them otherwise.
-el_status upload_order(el_plan p, hipStream_t s) {
-    const unsigned char *fast = p->fluid_path ? p->fast.data() : nullptr;
-    const std::vector<int> order = tile_order(p->tiles, fast, p->uni.data(), p->cols.data());
-    int *dst = reinterpret_cast<int *>(p->ws + p->L.tile_order);
-    HIP_TRY(hipMemcpyAsync(dst, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice, s), "tile order");
-    std::vector<unsigned char> fl(p->rec_tile.size(), 0);
-    for (size_t e = 0; e < fl.size(); ++e) fl[e] = fast && fast[p->rec_tile[e]] ? 1 : 0;
-    if (!fl.empty())
-        HIP_TRY(hipMemcpyAsync((void *)p->rec.fl, fl.data(), fl.size(), hipMemcpyHostToDevice, s), "receiver flags");
-    HIP_TRY(hipStreamSynchronize(s), "tile order");
-    p->tiles.order = dst;
+// The block list, the receiver corners' fluid flags and the points' places in the increments, with
+// the fluid tiles when the fluid update is enabled and without them otherwise.  Each setting has
+// tables of its own, made when it is first asked for, so a launch captured under one stays whole.
+template <typename T>
+el_status set_tables_t(el_plan p, Dev<T> &d, hipStream_t s) {
+    const int on = p->fluid_path ? 1 : 0;
+    const unsigned char *fast = on ? p->fast.data() : nullptr;
+    char *ws = p->ws;
+    d.incoff = (unsigned)(p->L.inc[on] >> 8);
+    p->rec.fl = reinterpret_cast<unsigned char *>(ws + p->L.rec_fl[on]);
+    p->rec.pos = reinterpret_cast<int *>(ws + p->L.csr_pos[on]);
+    p->tiles.order = ws + p->L.tile_order[on];
+    if (p->per[on] == 0 && p->tiles.ntiles > 0) {
+        const BlockList<T> list = block_list<T>(p->tiles, p->g.nx, p->g.ny, fast, p->uni.data(), p->lanes.data(),
+                                                reinterpret_cast<const T *>(p->med.data()), p->points);
+        HIP_TRY(hipMemcpyAsync(ws + p->L.tile_order[on], list.entries.get(), 8 * (size_t)list.per * sizeof(BlockEnt<T>),
+                               hipMemcpyHostToDevice, s), "block list");
+        HIP_TRY(launch_zero_inc(d, list.planes * kWaveX * kWaveY, s), "increments");
+        std::vector<unsigned char> fl(p->rec_tile.size(), 0);
+        for (size_t e = 0; e < fl.size(); ++e) fl[e] = fast && fast[p->rec_tile[e]] ? 1 : 0;
+        if (!fl.empty()) {
+            HIP_TRY(hipMemcpyAsync((void *)p->rec.fl, fl.data(), fl.size(), hipMemcpyHostToDevice, s), "receiver flags");
+            HIP_TRY(hipMemcpyAsync((void *)p->rec.pos, list.pos.data(), list.pos.size() * 4, hipMemcpyHostToDevice, s),
+                    "increments");
+        }
+        HIP_TRY(hipStreamSynchronize(s), "block list");
+        p->per[on] = list.per;
+    }
+    p->tiles.per = p->per[on];
     return EL_OK;
+}
+
+el_status set_tables(el_plan p, hipStream_t s) {
+    return p->g.precision == EL_F64 ? set_tables_t(p, p->dd, s) : set_tables_t(p, p->df, s);
 }
 
 el_status check_plan(el_plan p) {
@@ -558,9 +698,9 @@ el_status run_forward(el_plan p, Dev<T> &d, const T *p0, double *traces, hipStre
                       double *energy = nullptr) {
     const int M = p->g.nsteps, L = p->nrec;
     const int nb = 8 * p->tiles.per;
-    double *ekin = reinterpret_cast<double *>(p->ws + p->L.energy);   // per thread
-    double *ekb = ekin + (size_t)nb * kTileX * kTileY;                 // per block
-    double *epot = ekb + nb;
+    double *ekin = reinterpret_cast<double *>(p->ws + p->L.energy);   // per wavefront
+    double *epot = ekin + (size_t)nb * 4;                              // per block
+    double *ekb = epot + nb;                                           // per 64 blocks
     const Relax<T> &rx = plan_relax<T>(p);
     HIP_TRY(launch_zero_state(d, s), "zero state");
     HIP_TRY(launch_relax_zero(p->tiles, rx, s), "relaxation state");
@@ -594,16 +734,16 @@ el_status run_adjoint(el_plan p, Dev<T> &d, const double *y, T *out, hipStream_t
     HIP_TRY(timed(p, EL_K_SCATTER, M - 1, s, [&] { return launch_scatter(d, p->rec, y + (size_t)(M - 1) * L, s); }),
             "scatter");
     for (int m = M - 1; m >= 1; --m) {
-        HIP_TRY(timed(p, EL_K_ADJ_VELOCITY, m, s, [&] { return launch_adj_velocity(d, p->tiles, s); }),
+        // the adjoint velocity launch also forms the increments Theta^T y of row m-1, which the
+        // adjoint stress launch adds
+        HIP_TRY(timed(p, EL_K_ADJ_VELOCITY, m, s,
+                      [&] { return launch_adj_velocity(d, p->tiles, s, &p->rec, y + (size_t)(m - 1) * L); }),
                 "adjoint velocity pass");
         // the transposed relaxation sits between the transposed stress and velocity updates of
         // the step (the forward applies R between its velocity and stress updates)
         if (rx.L > 0)
             HIP_TRY(timed(p, EL_K_RELAX, m, s, [&] { return launch_relax(d, p->tiles, rx, true, s); }), "relaxation");
-        // the adjoint stress launch also adds Theta^T y of row m-1 (launch_adj_stress)
-        HIP_TRY(timed(p, EL_K_ADJ_STRESS, m, s,
-                      [&] { return launch_adj_stress(d, p->tiles, s, &p->rec, y + (size_t)(m - 1) * L); }),
-                "adjoint stress pass");
+        HIP_TRY(timed(p, EL_K_ADJ_STRESS, m, s, [&] { return launch_adj_stress(d, p->tiles, s); }), "adjoint stress pass");
     }
     if (p->fluid_path && p->fast_tiles > 0) HIP_TRY(launch_fluid_fill(d, p->tiles, s), "fluid fill");
     HIP_TRY(launch_extract(d, out, s), "extract");
@@ -724,7 +864,7 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
                               std::min(t.zc, grid->nz - bz * t.zc);
         }
         // a point keeps its element index in 30 bits
-        const long long elements = (long long)(grid->precision == EL_F64 ? p->dd.plane : p->df.plane) * (grid->nz + 4);
+        const long long elements = (long long)(grid->precision == EL_F64 ? p->dd.plane() : p->df.plane()) * (grid->nz + 4);
         if (elements > (long long)kRelaxElemMask + 1)
             return bail(fail(EL_EINVAL, "relaxation needs a padded grid of at most 2^30 elements (%lld)", elements));
         e = hipMemcpyAsync(p->ws + L.relax_off, roff.data(), roff.size() * sizeof(long long), hipMemcpyHostToDevice, s);
@@ -741,14 +881,16 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
         unsigned char *flags = reinterpret_cast<unsigned char *>(p->ws + L.tile_flags);
         unsigned char *uflags = flags + p->tiles.ntiles;
         unsigned long long *lanes = reinterpret_cast<unsigned long long *>(p->ws + L.tile_lanes);
-        p->tiles.lanes = lanes;
+        void *media = p->ws + L.tile_media;
         e = grid->precision == EL_F64
-                ? launch_classify(p->dd, p->tiles, flags, uflags, const_cast<double *>(p->dd.med), lanes, s)
-                : launch_classify(p->df, p->tiles, flags, uflags, const_cast<float *>(p->df.med), lanes, s);
+                ? launch_classify(p->dd, p->tiles, flags, uflags, static_cast<double *>(media), lanes, s)
+                : launch_classify(p->df, p->tiles, flags, uflags, static_cast<float *>(media), lanes, s);
+        p->med.assign(4 * (size_t)p->tiles.ntiles * (grid->precision == EL_F64 ? 8 : 4), 0);
+        if (e == hipSuccess) e = hipMemcpyAsync(p->med.data(), media, p->med.size(), hipMemcpyDeviceToHost, s);
         p->fast.assign(p->tiles.ntiles, 0);
         p->uni.assign(p->tiles.ntiles, 0);
-        p->cols.assign(p->tiles.ntiles, 0);
-        std::vector<unsigned long long> hl((size_t)2 * kTileY * p->tiles.ntiles, 0);
+        p->lanes.assign((size_t)2 * kTileY * p->tiles.ntiles, 0);
+        std::vector<unsigned long long> &hl = p->lanes;
         if (e == hipSuccess && p->tiles.ntiles > 0)
             e = hipMemcpyAsync(hl.data(), lanes, hl.size() * 8, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess && p->tiles.ntiles > 0)
@@ -767,6 +909,8 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
             const int hi = std::max(0, c1 - std::max(c0, nn - P));
             return lo + hi;
         };
+        // the columns of a tile row before column c
+        auto below = [](int c) { return c <= 0 ? 0ull : (c >= 64 ? ~0ull : (1ull << c) - 1ull); };
         for (int q = 0; q < t.ntiles; ++q) {
             if (!p->fast[q]) {
                 // fluid columns of a general tile: all their cells take the fluid update
@@ -775,16 +919,15 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
                 for (int row = 0; row < kTileY; ++row) {
                     const unsigned long long m = hl[(size_t)kTileY * q + row];
                     if (!m) continue;
-                    p->cols[q] = 1;
                     const unsigned long long um = hl[(size_t)kTileY * ((size_t)t.ntiles + q) + row];
                     p->uniform_cells += (long long)__builtin_popcountll(um) * dep;
-                    for (int b = 0; b < 64; ++b) {
-                        if (!((m >> b) & 1ull)) continue;
-                        const int i = bx * kTileX + b, j = by * kTileY + row;
-                        p->column_cells += dep;
-                        p->fast_layer_cells += (long long)in_layers(i, i + 1, n[0]) * dep +
-                                               (long long)in_layers(j, j + 1, n[1]) * dep + in_layers(z0, z0 + dep, n[2]);
-                    }
+                    const int x0 = bx * kTileX, j = by * kTileY + row;
+                    const long long cols = __builtin_popcountll(m);
+                    const long long xcols = P <= 0 ? 0
+                                                   : __builtin_popcountll(m & below(P - x0)) +
+                                                         __builtin_popcountll(m & ~below(n[0] - P - x0));
+                    p->column_cells += cols * dep;
+                    p->fast_layer_cells += (xcols + cols * in_layers(j, j + 1, n[1])) * dep + cols * in_layers(z0, z0 + dep, n[2]);
                 }
                 continue;
             }
@@ -797,13 +940,13 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
             for (int a = 0; a < 3; ++a)
                 p->fast_layer_cells += (long long)in_layers(c0[a], c0[a] + w[a], n[a]) * w[(a + 1) % 3] * w[(a + 2) % 3];
             // s22 (s33) is stored only on two-cell bands along y (z) faces next to general tiles
-            const int edges = tile_edges(t, p->fast.data(), q) >> kEdgeShift;
+            const int edges = (int)tile_edges(t, p->fast.data(), q);
             for (int a = 1; a < 3; ++a) {
                 const int lo = (edges >> (2 * (a - 1))) & 1, hi = (edges >> (2 * (a - 1) + 1)) & 1;
                 p->fast_skipped += (long long)std::max(0, w[a] - 2 * lo - 2 * hi) * w[(a + 1) % 3] * w[(a + 2) % 3];
             }
         }
-        st = upload_order(p, s);
+        st = set_tables(p, s);
         if (st != EL_OK) return bail(st);
     }
     e = hipStreamSynchronize(s);
@@ -936,7 +1079,7 @@ el_status el_plan_field(el_plan p, int32_t id, void **ptr, size_t *count) {
     if (!p) return fail(EL_EINVAL, "plan is NULL");
     if (id < 0 || id >= NFIELD) return fail(EL_EINVAL, "field id %d outside 0..8", id);
     if (!ptr || !count) return fail(EL_EINVAL, "ptr or count is NULL");
-    *ptr = p->ws + p->L.field[id];
+    *ptr = p->ws + p->L.vol[id];
     *count = (size_t)make_vol(p->g.nx, p->g.ny, p->g.nz).total;
     return EL_OK;
 }
@@ -957,7 +1100,7 @@ el_status el_plan_fluid_path(el_plan p, int32_t enable, el_fluid_stats *stats) {
     if (enable >= 0 && (enable != 0) != p->fluid_path) {
         HIP_TRY(hipEventSynchronize(p->done), "wait for the plan's previous operation");
         p->fluid_path = enable != 0;
-        st = upload_order(p, nullptr);
+        st = set_tables(p, nullptr);
         if (st != EL_OK) return st;
     }
     if (stats) {

@@ -62,8 +62,8 @@ el_status hipf(hipError_t e, const char *what) {
 
 // One time step with the trace row taken from the device counter: the forward velocity pass
 // gathers row *ctr (the stresses of the previous step) in extra blocks and the stress pass
-// advances the counter; the adjoint velocity pass steps it back and the adjoint stress pass
-// adds Theta^T y of that row.
+// advances the counter; the adjoint velocity pass forms the increments Theta^T y of row *ctr - 1
+// in extra blocks and the adjoint stress pass adds them and steps the counter back.
 template <typename T>
 hipError_t launch_step(el_plan p, const Dev<T> &d, int op, void *traces, int *ctr, hipStream_t s) {
     hipError_t e;
@@ -73,9 +73,9 @@ hipError_t launch_step(el_plan p, const Dev<T> &d, int op, void *traces, int *ct
         if (e == hipSuccess) e = launch_relax(d, p->tiles, rx, false, s);
         if (e == hipSuccess) e = launch_stress(d, p->tiles, s, ctr);
     } else {
-        e = launch_adj_velocity(d, p->tiles, s, ctr);
+        e = launch_adj_velocity(d, p->tiles, s, &p->rec, static_cast<const double *>(traces), ctr);
         if (e == hipSuccess) e = launch_relax(d, p->tiles, rx, true, s);
-        if (e == hipSuccess) e = launch_adj_stress(d, p->tiles, s, &p->rec, static_cast<const double *>(traces), ctr);
+        if (e == hipSuccess) e = launch_adj_stress(d, p->tiles, s, ctr);
     }
     return e;
 }

@@ -115,7 +115,7 @@ struct Batch {
 };
 
 // One grouped launch of `pass` over the members of b (pass 0 gathers the forward trace row of
-// the step each member is about to take; pass 3 adds Theta^T y of the adjoint row).
+// the step each member is about to take; pass 2 forms Theta^T y of the adjoint row).
 template <typename T>
 el_status grouped(el_group g, const Batch &b, int pass) {
     Grp<T, kGroupMax> gp{};
@@ -136,10 +136,12 @@ el_status grouped(el_group g, const Batch &b, int pass) {
             gp.row[q] = static_cast<double *>(mb.out) + (size_t)mb.steps * L;
             blocks += gather_blocks(L);
         }
-        if (pass == 3 && p->rec.npts > 0) {
-            // adjoint update k is m = M-1-k; its stress pass adds Theta^T y of row m-1
+        if (pass == 2 && p->rec.npts > 0) {
+            // adjoint update k is m = M-1-k; its velocity pass forms the increments Theta^T y of
+            // row m-1, which its stress pass adds
             gp.r[q] = p->rec;
             gp.row[q] = const_cast<double *>(static_cast<const double *>(mb.in)) + (size_t)(M - 2 - mb.steps) * L;
+            blocks += scatter_blocks(p->rec.npts);
         }
         blocks = (blocks + 7) / 8 * 8;
     }

@@ -19,6 +19,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <memory>
 #include <utility>
 #include <vector>
 
@@ -42,26 +43,47 @@ Vol make_vol(int nx, int ny, int nz);
 // Record the detail of a failure for el_last_error() and return the status.
 el_status set_error(el_status st, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 
-// Everything a stencil kernel needs, passed by value.
+constexpr int kNoPml = -8;
+
+// A plan's arrays and constants, passed to the kernels by value.  The arrays lie in the plan's
+// workspace at equal distances, so a base address and a few strides say where each one is (in
+// units of 256 bytes, which fit 32 bits): a stencil kernel loads this struct once, with a few
+// wide scalar loads, and forms addresses with scalar arithmetic.  With a pointer per array the
+// loops spent their time on scalar loads that each waited for the one before.
 template <typename T>
 struct Dev {
+    char *ws;                // workspace
+    unsigned vstr;           // volume arrays (9 fields, 4 maps): stride, the first at offset 0
+    unsigned moff[3], mstr[3];   // memory variables of each axis: first of six, stride
+    unsigned coff[3], cstr[3];   // C-PML coefficients of each axis: first of four, stride
+    unsigned incoff;         // increment blocks
     int nx, ny, nz;
     unsigned sy, sz;         // byte strides of +y and +z (the +x stride is sizeof(T))
-    unsigned origin;         // byte offset of cell (0,0,0)
-    int px;                  // row pitch (elements)
-    long long plane;         // plane size (elements)
+    int P;                   // C-PML cells per face, kNoPml = none (then no cell is in or near a layer)
+    int high[3], xw;         // boundary-slab storage (below)
     T dt, inv_dx;
-    T *f[NFIELD];            // u1, u2, u3, s11, s22, s33, s23, s13, s12 (padded)
-    const T *lam, *mu, *rho, *alpha;   // cell maps (padded, edge-replicated)
-    int P;                   // C-PML cells per face, 0 = none
-    int hi[3];               // first index of the high boundary slab per axis: n - 1 - P
-    int W;                   // slab planes per axis: 2 (P + 7)
-    const T *pa[3][2];       // PML a per axis, [0] integer / [1] half positions
-    const T *pb[3][2];       // PML b
-    T *mem[3][6];            // boundary-slab memory variables of axis j:
-                             //   mem[j][i]     = phi^{ij} (u^i point),
-                             //   mem[j][3 + i] = psi^{ij} (sigma^{ij} point)
-    const T *med;            // per tile: lambda, rho, alpha, 0 of a uniform fluid tile
+
+    __host__ __device__ T *at(unsigned off256) const { return reinterpret_cast<T *>(ws + ((unsigned long long)off256 << 8)); }
+    __host__ __device__ T *f(int id) const { return at((unsigned)id * vstr); }    // wavefields (padded)
+    // cell maps (padded, edge-replicated)
+    __host__ __device__ T *lam() const { return f(NFIELD); }
+    __host__ __device__ T *mu() const { return f(NFIELD + 1); }
+    __host__ __device__ T *rho() const { return f(NFIELD + 2); }
+    __host__ __device__ T *alpha() const { return f(NFIELD + 3); }
+    // boundary-slab memory variables of axis j: mem(j, i) = phi^{ij} (u^i point),
+    // mem(j, 3 + i) = psi^{ij} (sigma^{ij} point)
+    __host__ __device__ T *mem(int j, int q) const { return at(moff[j] + (unsigned)q * mstr[j]); }
+    // C-PML a and b along x (0) and y (1), h = 0 integer / 1 half positions; along z the pairs (a, b)
+    __host__ __device__ T *pa(int j, int h) const { return at(coff[j] + 2u * (unsigned)h * cstr[j]); }
+    __host__ __device__ T *pb(int j, int h) const { return at(coff[j] + (2u * (unsigned)h + 1u) * cstr[j]); }
+    __host__ __device__ T *zab(int h) const { return at(coff[2] + 2u * (unsigned)h * cstr[2]); }
+    // adjoint increments Theta^T y of one trace row: a block of zc x 64 elements (plane, lane) per
+    // sub-tile with scatter points, zero off the points
+    __host__ __device__ T *inc() const { return at(incoff); }
+    __host__ __device__ int hi(int a) const { return (a == 0 ? nx : (a == 1 ? ny : nz)) - 1 - P; }   // first index of the high slab
+    __host__ __device__ int W() const { return P > 0 ? 2 * (P + 7) : 0; }   // slab planes per axis
+    __host__ __device__ int px() const { return (int)(sy / sizeof(T)); }    // row pitch (elements)
+    __host__ __device__ long long plane() const { return (long long)(sz / sizeof(T)); }
 };
 
 // Boundary-slab storage of the C-PML memory variables.  Along each axis the variables live on
@@ -70,78 +92,108 @@ struct Dev {
 // W = 2 (P + 7) planes in all.  Cells of the layer (c <= P or c >= hi) own their value; the
 // extra planes let a 4-tap difference centred on any cell within two planes of a layer read
 // its taps without tests, and hold zeros (the adjoint keeps its memory variables multiplied
-// by the layer coefficient a, which vanishes outside the layer).  When both ranges cover a
-// layer cell (fewer than ten planes between the layers) the cell writes both copies.
-__host__ __device__ inline int slab_lo(int c) { return c + 2; }
-__host__ __device__ inline int slab_hi(int c, int P, int hi) { return c - (hi - 4) + P + 7; }
-// primary slab coordinate of a layer cell, -1 outside the layer
-__host__ __device__ inline int slab_own(int c, int P, int hi) {
-    return c <= P ? slab_lo(c) : (c >= hi ? slab_hi(c, P, hi) : -1);
-}
-// second copy of a layer cell covered by both ranges, -1 otherwise
-__host__ __device__ inline int slab_twin(int c, int P, int hi) {
-    return (c <= P && c >= hi - 4) ? slab_hi(c, P, hi) : ((c >= hi && c <= P + 4) ? slab_lo(c) : -1);
+// by the layer coefficient a, which vanishes outside the layer).  Where the two ranges would
+// overlap (n <= 2P + 9, fewer than ten planes between the layers) one range -2 .. n+1 holds them
+// all at slab coordinates c + 2 (n + 4 < W); d.high is the slab coordinate of cell 0 in the
+// range that a cell near the high layer uses.
+// slab coordinate of a layer cell, -1 outside the layer
+template <typename T>
+__host__ __device__ inline int slab_own(const Dev<T> &d, int a, int c) {
+    return c <= d.P ? c + 2 : (c >= d.hi(a) ? c + d.high[a] : -1);
 }
 // slab coordinate of a cell whose 4-tap stencil along the axis reaches a layer, -1 otherwise
-__host__ __device__ inline int slab_near(int c, int P, int hi) {
-    return c <= P + 2 ? slab_lo(c) : (c >= hi - 2 ? slab_hi(c, P, hi) : -1);
+template <typename T>
+__host__ __device__ inline int slab_near(const Dev<T> &d, int a, int c) {
+    return c <= d.P + 2 ? c + 2 : (c >= d.hi(a) - 2 ? c + d.high[a] : -1);
 }
 // Element order: axis x as [side][k][j][s'] with s' the coordinate within the side's
-// P + 7 planes (a tile's rows of one side are contiguous; the two sides are touched by
-// different tiles), axis y as [k][s][i], axis z as [s][j][i].
+// d.xw = P + 7 planes (a tile's rows of one side are contiguous; the two sides are touched by
+// different tiles; a single range is one side of d.xw = W planes), axis y as [k][s][i], axis z
+// as [s][j][i].
 template <typename T>
 __device__ inline unsigned slab_byte(const Dev<T> &d, int axis, int s, int i, int j, int k) {
     unsigned e;
     if (axis == 0) {
-        const int hw = d.W >> 1;
-        const int side = s >= hw ? 1 : 0;
-        e = (((unsigned)side * d.nz + k) * d.ny + j) * hw + (s - side * hw);
+        const int side = s >= d.xw ? 1 : 0;
+        e = (((unsigned)side * d.nz + k) * d.ny + j) * d.xw + (s - side * d.xw);
     } else {
-        e = axis == 1 ? ((unsigned)k * d.W + s) * d.nx + i : ((unsigned)s * d.ny + j) * d.nx + i;
+        e = axis == 1 ? ((unsigned)k * d.W() + s) * d.nx + i : ((unsigned)s * d.ny + j) * d.nx + i;
     }
     return e * (unsigned)sizeof(T);
 }
-// byte stride between neighbouring slab coordinates of an axis
-template <typename T>
-__device__ inline unsigned slab_stride(const Dev<T> &d, int axis) {
-    return (unsigned)sizeof(T) * (axis == 0 ? 1u : (axis == 1 ? (unsigned)d.nx : (unsigned)d.nx * d.ny));
-}
-
 // Column tiles of the stencil passes: kTileX x kTileY cells in x-y, a chunk of zc planes in z.
+// A tile is four sub-tiles of kWaveX x kWaveY columns, one wavefront wide: sub-tile s covers
+// columns (s & 1) kWaveX .. and rows (s >> 1) kWaveY .. of the tile.
 constexpr int kTileX = 64;
 constexpr int kTileY = 4;
+constexpr int kWaveX = 32;
+constexpr int kWaveY = 2;
+// An entry of the block list: planes of a tile column and what its block does there.
+// A general entry (kBlkGen) updates one sub-tile (kBlkSubShift), a wavefront per velocity
+// component or per kind of stress.  A fluid entry updates the fluid sub-tiles set in the four bits from kBlkMaskShift, a wavefront
+// each; those also set from kBlkUniShift have uniform lambda, rho and alpha (k_classify), taken
+// from a per-tile table instead of the maps.  The general update differences s22 only along y and
+// s33 only along z, with taps reaching two cells into a neighbouring tile, so a fluid tile stores
+// s22 only on two-row bands along the y faces (bits 0, 1 from kBlkEdgeShift: lower, upper) and
+// s33 only on two-plane bands along the z faces (bits 2, 3) it shares with tiles that are not
+// fluid; kBlkKeep: the fluid sub-tiles of a tile that is not fluid store both everywhere.
+// Of these planes, the sub-tiles set in the four bits from kBlkIncShift hold scatter points: the
+// first one's increments (Dev::inc) begin at plane slot, the next one's z1 - z0 planes on.
+// kBlkFirst marks the first of the entries that cover the same planes of a tile, kBlkFast the (only)
+// entry of fluid ones.
+// An entry is one 64-byte line, read with one scalar load: what a block needs before its first
+// vector load.
+template <typename T>
+struct alignas(64) BlockEnt {
+    int bx, by, z0, z1;      // tile along x and y, planes
+    unsigned flags;          // 0: padding block
+    int slot;                // first plane of the tile's increments (kWaveX kWaveY elements each)
+    unsigned fluid[kWaveY];  // kBlkGen: fluid columns of the sub-tile's rows
+    unsigned uniform[kWaveY];// those of the tile's reference medium (k_classify)
+    T lam, rho, alpha;       // a uniform tile's medium, a general tile's reference medium (k_classify)
+};
+constexpr unsigned kBlkGen = 1u << 0;
+constexpr int kBlkSubShift = 1;
+constexpr int kBlkMaskShift = 4;
+constexpr int kBlkUniShift = 8;
+constexpr int kBlkEdgeShift = 12;
+constexpr unsigned kBlkKeep = 1u << 16;
+constexpr unsigned kBlkFirst = 1u << 17;
+constexpr unsigned kBlkFast = 1u << 18;
+constexpr int kBlkIncShift = 20;
 struct Tiles {
     int ntx, nty, nzc, zc;   // tiles along x and y, z chunks, planes per chunk
+    int nz, zb;              // planes, planes per block
+    int shortest() const { return zb < 3 ? 2 : zb - 1; }   // planes of a block, unless its run has fewer; s33's bands have two
+    int longest() const { return 2 * shortest() + zb - 2; }
+    bool bands() const { return nty >= 8 && nz >= 8 * zb; }                 // see piece_xcd
+    int run() const { return (int)(((long long)ntx * nty * ((nz + zb - 1) / zb) + 511) / 512); }
     int ntiles;              // ntx * nty * nzc
-    int per;                 // tiles per XCD: the grid has 8 * per blocks
-    const int *order;        // device: tile of each block (-1 for a padding block)
-    const unsigned long long *lanes;   // device: per tile and row, its fluid columns; then, per tile
-                                       // and row, those of the tile's reference medium (k_classify)
+    int cap;                 // entries per XCD at most
+    int per;                 // entries per XCD: the grid has 8 * per blocks
+    const void *order;       // device: the block list (BlockEnt<T>); entry b is block b's, on XCD b % 8
 };
 Tiles make_tiles(int nx, int ny, int nz);
-// XCD (0..7) that processes tile q; blocks run on XCD blockIdx % 8.
-int tile_xcd(const Tiles &t, int q);
-// Tile of each block (8 * per entries, -1 for padding blocks): the tiles of XCD x in z-major
-// order at entries x, x + 8, x + 16, ...  An entry holds the tile number in its low
-// kEdgeShift bits and carries kFastTile when fast[q] is set (fast may be null): the block
-// then runs the fluid update of the tile.  The four bits from kEdgeShift up mark which face
-// neighbours of a fluid tile along y (y-, y+) and z (z-, z+) take the general update.  The
-// general loop differences s22 only along y and s33 only along z, with taps reaching two
-// cells into a neighbouring tile, so the fluid update stores s22 only on two-row bands
-// along such y faces and s33 only on two-plane bands along such z faces.
-// kUniformTile marks a fluid tile whose lambda, rho and alpha are constant over the cells
-// its loops read (k_classify): they come from a per-tile table instead of the maps.
-// kColumnTile marks a tile that is not fluid but has fluid columns (Tiles::lanes): the
-// lanes of those columns run the fluid update.
-constexpr int kFastTile = 1 << 30;
-constexpr int kUniformTile = 1 << 29;
-constexpr int kColumnTile = 1 << 28;
-constexpr int kEdgeShift = 24;
-constexpr int kTileMask = (1 << kEdgeShift) - 1;
-std::vector<int> tile_order(const Tiles &t, const unsigned char *fast, const unsigned char *uni,
-                            const unsigned char *cols);
-// Bits kEdgeShift.. of tile q's entry (0 unless q is a fluid tile).
-int tile_edges(const Tiles &t, const unsigned char *fast, int q);
+// XCD (0..7) that processes a piece of tile row by from plane z on; blocks run on XCD blockIdx % 8.
+int piece_xcd(const Tiles &t, int by, int z, long long index);
+// The block list, padded to 8 * per entries: the entries of XCD x at x, x + 8, x + 16, ..., in
+// z-major order.  fast: per tile, 1 if it is fluid (null: every tile takes the general update).
+// lanes: per tile and row, its fluid columns; then, per tile and row, those of the tile's
+// reference medium; med: per tile, lambda, rho, alpha, 0 (k_classify).  points: i, j, k of the
+// scatter points.
+template <typename T>
+struct BlockList {
+    std::unique_ptr<BlockEnt<T>[]> entries;
+    int per = 0;
+    long long planes = 0;    // increment planes of kWaveX x kWaveY elements
+    std::vector<int> pos;    // each point's element in them
+};
+template <typename T>
+BlockList<T> block_list(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned char *uni,
+                        const unsigned long long *lanes, const T *med, const std::vector<int> &points);
+// Faces of fluid tile q shared with tiles that are not fluid: bits 0, 1 along y, 2, 3 along z
+// (lower, upper); 0 unless q is a fluid tile.
+unsigned tile_edges(const Tiles &t, const unsigned char *fast, int q);
 
 // Relaxation mechanisms of the frequency-dependent absorption (el_relaxation): after every
 // velocity pass the tiles holding a velocity point with beta > 0 apply the pointwise
@@ -179,12 +231,7 @@ struct Rec {
     const int *row;          // [npts + 1] offsets into ent_rec / ent_w
     const int *ent_rec;      // receiver of each entry
     const double *ent_w;     // weight of each entry
-    // scatter points by stencil tile and column: tslot[t] is -1 for a tile without points,
-    // else s, and the points of column (c, r) of the tile (key c + kTileX r) are
-    // tpts[loff[s (kTileX kTileY + 1) + key] .. loff[... + key + 1])
-    const int *tslot;        // [ntiles]
-    const int *loff;         // [slots][kTileX kTileY + 1]
-    const int *tpts;         // [npts] point numbers sorted by (tile, key)
+    const int *pos;          // [npts] element of each point in the increment blocks (Dev::inc)
 };
 
 // Receiver gather: p_hat_m[l] = -sum_c w_lc (s11 + s22 + s33)[c]  (Sec. 3, eq. interpgrid), in
@@ -194,8 +241,8 @@ struct Rec {
 template <typename T>
 __device__ __forceinline__ double trace_at(const Dev<T> &d, const Rec &r, int e) {
     const long long q = r.idx[e];
-    const double s11 = (double)d.f[S11][q];
-    return r.fl[e] ? 3.0 * s11 : s11 + (double)d.f[S22][q] + (double)d.f[S33][q];
+    const double s11 = (double)d.f(S11)[q];
+    return r.fl[e] ? 3.0 * s11 : s11 + (double)d.f(S22)[q] + (double)d.f(S33)[q];
 }
 // The receivers of gather block gb (256 threads: 4 wavefronts, 32 receivers) into out[].
 template <typename T>
@@ -213,32 +260,23 @@ __device__ __forceinline__ void gather_block(const Dev<T> &d, const Rec &r, doub
 }
 inline int gather_blocks(int nrec) { return ((nrec + 7) / 8 + 3) / 4; }
 
-// s_kk += Theta^T y_m at point t of the grid-point-major table (entries summed in a fixed
-// order).  With the adjoint stress kept as w = C s this adds (3 lambda + 2 mu) delta to w11,
-// w22, w33, and the normal adjoint memory variables, which hold a (b psi~ + dt w) for the
-// coming step, receive a dt times the same increment.
+// Theta^T y at point t of the grid-point-major table for the trace row y (entries summed in a
+// fixed order): with the adjoint stress kept as w = C s it adds 3 lambda + 2 mu times this value
+// to w11, w22 and w33.
 template <typename T>
-__device__ __forceinline__ void scatter_point(const Dev<T> &d, const Rec &r, const double *y, int t) {
+__device__ __forceinline__ T scatter_value(const Rec &r, const double *y, int t) {
     double acc = 0.0;
     for (int e = r.row[t]; e < r.row[t + 1]; ++e) acc += r.ent_w[e] * y[r.ent_rec[e]];
-    const long long q = r.pt[t];
-    const T dw = T(-acc) * (T(3) * d.lam[q] + T(2) * d.mu[q]);
-    d.f[S11][q] += dw;
-    d.f[S22][q] += dw;
-    d.f[S33][q] += dw;
-    if (d.P > 0) {
-        const int crd[3] = {r.ptc[3 * t], r.ptc[3 * t + 1], r.ptc[3 * t + 2]};
-        for (int a = 0; a < 3; ++a) {
-            const int s = slab_own(crd[a], d.P, d.hi[a]);
-            if (s < 0) continue;
-            const T inc = d.pa[a][0][crd[a]] * d.dt * dw;
-            T *g = d.mem[a][3 + a];
-            g[slab_byte(d, a, s, crd[0], crd[1], crd[2]) / sizeof(T)] += inc;
-            const int tw = slab_twin(crd[a], d.P, d.hi[a]);
-            if (tw >= 0) g[slab_byte(d, a, tw, crd[0], crd[1], crd[2]) / sizeof(T)] += inc;
-        }
-    }
+    return T(-acc);
 }
+// The increments of scatter block sb (256 points) into the plan's increment blocks, where the
+// adjoint stress pass that follows picks them up.
+template <typename T>
+__device__ __forceinline__ void scatter_block(const Dev<T> &d, const Rec &r, const double *y, int sb) {
+    const int t = sb * 256 + (int)threadIdx.x;
+    if (t < r.npts) d.inc()[r.pos[t]] = scatter_value<T>(r, y, t);
+}
+inline int scatter_blocks(int npts) { return (npts + 255) / 256; }
 
 // Arguments of a stencil launch over the tiles of G plans of one precision (G = 1: a plan's
 // own forward passes; G = kGroupMax: the grouped passes of el_group, and a plan's own
@@ -246,7 +284,8 @@ __device__ __forceinline__ void scatter_point(const Dev<T> &d, const Rec &r, con
 // first[q] is a multiple of 8, so that the member's block b - first[q] runs on XCD
 // (b - first[q]) % 8 as its tile order assumes.  Entries past the last member repeat the
 // total block count (or lie beyond every block).  row[q]: the trace row that member's gather
-// blocks write (forward velocity launch) or its adjoint stress launch scatters, or null.
+// blocks write (forward velocity launch) or its scatter blocks read (adjoint velocity launch), or
+// null.
 constexpr int kGroupMax = 4;
 template <typename T, int G>
 struct Grp {
@@ -260,6 +299,10 @@ struct Grp {
 template <typename T, int G>
 __device__ __forceinline__ int member_of(const Grp<T, G> &g) {
     int q = 0;
+    if (G == 1) {
+        asm("" : "+s"(q));
+        return q;
+    }
 #pragma unroll
     for (int k = 1; k < G; ++k) q += (int)blockIdx.x >= g.first[k] ? 1 : 0;
     return q;
@@ -267,20 +310,21 @@ __device__ __forceinline__ int member_of(const Grp<T, G> &g) {
 
 // Workspace layout (byte offsets), computed identically for sizing and binding.
 struct Layout {
-    size_t field[NFIELD];
-    size_t map[4];           // lam, mu, rho, alpha
-    size_t mem[3][6];
-    size_t pa[3][2], pb[3][2];
-    size_t rec_idx, rec_w, rec_fl, csr_pt, csr_ptc, csr_row, csr_rec, csr_w, csr_tslot, csr_loff, csr_tpts;
+    size_t vol[NFIELD + 4];  // wavefields, then the maps lam, mu, rho, alpha: equal strides from 0
+    size_t mem[3][6];        // equal strides along each axis
+    size_t coef[3][4];       // C-PML a, b at integer, then at half positions: equal strides along each axis (z: pairs
+                             // (a, b) over both arrays of a position)
+    size_t rec_idx, rec_w, csr_pt, csr_ptc, csr_row, csr_rec, csr_w;
+    size_t rec_fl[2], csr_pos[2], inc[2];   // without, with the fluid update (as tile_order)
     size_t stats;            // media statistics (16 doubles)
     size_t counter;          // device step counter of captured step graphs
-    size_t tile_order;       // tile of each stencil block
+    size_t tile_order[2];    // block lists of the stencil passes (8 * cap entries)
     size_t tile_flags;       // per tile: 1 if the fluid update applies; then per tile: 1 if uniform
     size_t tile_media;       // per tile: lambda, rho, alpha, 0 (elements of the plan's precision)
     size_t tile_lanes;       // per tile and row: 64-bit masks of fluid columns, then of uniform ones
     size_t partial;          // reduction partials
-    size_t energy;           // modified energy: kinetic part of each thread of the tile blocks, then
-                             // kinetic and potential part of each tile block
+    size_t energy;           // modified energy: kinetic part of each wavefront of the velocity blocks,
+                             // sums of those, and potential part of each block
     size_t relax_map;        // alpha_r (padded cell map), with relaxation mechanisms only
     size_t relax_flag;       // per tile: relaxation applies
     size_t relax_count;      // per tile: velocity points with beta > 0 (int)
@@ -309,34 +353,34 @@ template <typename T> hipError_t launch_inject(const Dev<T> &d, const T *p0, hip
 // The forward velocity launch can also gather a trace row (grow != null) from the stresses it
 // reads and does not write: extra blocks after the tiles' run gather_block.
 // epart != null: the launch also writes the kinetic part of the modified energy, one double per
-// thread of every tile block (8 * per * kTileX * kTileY doubles); launch_energy_pot writes the
-// potential part, one double per tile block; launch_energy_final sums the threads' parts per
-// block into kin_block, then everything into *out.
+// wavefront of every block (4 per block, 8 * per blocks); launch_energy_pot writes the potential
+// part, one double per block; launch_energy_final sums the wavefronts' parts in groups into
+// kin_block (one double per 64 blocks), then everything into *out.
 // ctr != null (captured step graphs): a device step counter.  The velocity launch gathers row
 // *ctr of the traces at grow and the stress launch then advances the counter; the adjoint
-// velocity launch steps it back by one and the scatter then reads row *ctr of the traces at y.
+// velocity launch scatters row *ctr - 1 of the traces at y and the adjoint stress launch then
+// steps the counter back.
 template <typename T> hipError_t launch_velocity(const Dev<T> &d, const Tiles &tl, hipStream_t s,
                                                  const Rec *r = nullptr, double *grow = nullptr,
                                                  double *epart = nullptr, int *ctr = nullptr);
 template <typename T> hipError_t launch_energy_pot(const Dev<T> &d, const Tiles &tl, double *epart, hipStream_t s);
-hipError_t launch_energy_final(const double *kin_thread, double *kin_block, const double *pot, int nb, double *out,
+hipError_t launch_energy_final(const double *kin, double *kin_block, const double *pot, int nb, double *out,
                                hipStream_t s);
 template <typename T> hipError_t launch_stress(const Dev<T> &d, const Tiles &tl, hipStream_t s, int *ctr = nullptr);
 template <typename T> hipError_t launch_gather(const Dev<T> &d, const Rec &r, double *trace_row, hipStream_t s);
+// The adjoint velocity launch can also form the increments Theta^T y of a trace row (r and y
+// non-null) in extra blocks after the tiles'; the adjoint stress launch adds them to the cells it
+// has updated.
 template <typename T> hipError_t launch_adj_velocity(const Dev<T> &d, const Tiles &tl, hipStream_t s,
+                                                     const Rec *r = nullptr, const double *y = nullptr,
                                                      int *ctr = nullptr);
-// The adjoint stress launch also applies the scatter of trace row y (r and y non-null): each
-// lane, after its column's update, adds Theta^T y at the scatter points of its own cells (the
-// values it has just written), in the order and arithmetic of launch_scatter.  ctr != null:
-// y is the whole trace array and the row is *ctr (stepped back by the adjoint velocity launch).
-template <typename T> hipError_t launch_adj_stress(const Dev<T> &d, const Tiles &tl, hipStream_t s,
-                                                   const Rec *r = nullptr, const double *y = nullptr,
-                                                   int *ctr = nullptr);
-template <typename T> hipError_t launch_scatter(const Dev<T> &d, const Rec &r, const double *y, hipStream_t s,
-                                                const int *ctr = nullptr);
+template <typename T> hipError_t launch_adj_stress(const Dev<T> &d, const Tiles &tl, hipStream_t s, int *ctr = nullptr);
+// Theta^T y of the first row, into the zero state.
+template <typename T> hipError_t launch_scatter(const Dev<T> &d, const Rec &r, const double *y, hipStream_t s);
+template <typename T> hipError_t launch_zero_inc(const Dev<T> &d, long long n, hipStream_t s);
 // Grouped passes (el_group): pass 0 velocity (with the gather blocks of members whose row is
-// set), 1 stress, 2 adjoint velocity, 3 adjoint stress (with the scatter of members whose row
-// is set); g.first from the members' 8 * per blocks (plus gather blocks for pass 0).
+// set), 1 stress, 2 adjoint velocity (with the scatter blocks of members whose row is set), 3
+// adjoint stress; g.first from the members' 8 * per blocks plus gather or scatter blocks.
 template <typename T> hipError_t launch_group_pass(const Grp<T, kGroupMax> &g, int pass, hipStream_t s);
 template <typename T> hipError_t launch_extract(const Dev<T> &d, T *p, hipStream_t s);
 template <typename T> hipError_t launch_fluid_fill(const Dev<T> &d, const Tiles &tl, hipStream_t s);
@@ -379,13 +423,17 @@ struct el_plan_ {
     el::Tiles tiles;
     std::vector<unsigned char> fast;   // per tile: the fluid update applies (host copy)
     std::vector<unsigned char> uni;    // per tile: fluid with uniform lambda, rho, alpha (host copy)
-    std::vector<unsigned char> cols;   // per tile: not fluid, with fluid columns (host)
+    std::vector<unsigned long long> lanes;   // per tile and row: its fluid columns, then those of its
+                                             // reference medium (host copy)
+    std::vector<char> med;             // per tile: lambda, rho, alpha, 0 (host copy, of the plan's precision)
     long long column_cells = 0;        // cells of fluid columns in such tiles
     long long uniform_cells = 0;       // cells of uniform fluid tiles
     long long fast_tiles = 0, fast_cells = 0;
     long long fast_layer_cells = 0;    // sum over axes of fluid-tile cells in that axis's C-PML layers
     long long fast_skipped = 0;        // s22 and s33 stores a fluid stress pass leaves out
     std::vector<int> rec_tile;         // [L][8] tile of each receiver corner (host)
+    std::vector<int> points;           // i, j, k of the scatter points (host)
+    int per[2] = {};                   // Tiles::per of the tables without, with the fluid update (0: not made yet)
     bool fluid_path = true;            // use the fluid update where it applies
     hipEvent_t done;
     double cmax;

@@ -5,6 +5,8 @@
 // staggered density) and w = C s (Voigt stiffness times the stress adjoint),
 // so the scatter of Theta^T y adds C applied to an isotropic increment and
 // the extraction tau'^T v_0 = -(s11+s22+s33)/3 recovers tr s from w.
+#include <algorithm>
+
 #include "el_impl.h"
 
 namespace el {
@@ -18,12 +20,12 @@ namespace el {
 template <typename T>
 __global__ void k_convert_maps(Dev<T> d, const float *lam, const float *mu, const float *rho, const float *alpha,
                                long long total) {
-    const long long plane = d.plane;
+    const long long plane = d.plane();
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
          e += (long long)gridDim.x * blockDim.x) {
         const long long zp = e / plane;
         const long long rem = e - zp * plane;
-        const int y = (int)(rem / d.px), x = (int)(rem - (long long)y * d.px);
+        const int y = (int)(rem / d.px()), x = (int)(rem - (long long)y * d.px());
         const int z = (int)zp - 2;
         T vl = T(0), vm = T(0), vr = T(0), va = T(0);
         if (z >= 0 && z <= d.nz && y <= d.ny && x <= d.nx) {
@@ -34,17 +36,17 @@ __global__ void k_convert_maps(Dev<T> d, const float *lam, const float *mu, cons
             vr = T(rho[src]);
             va = T(alpha[src]);
         }
-        const_cast<T *>(d.lam)[e] = vl;
-        const_cast<T *>(d.mu)[e] = vm;
-        const_cast<T *>(d.rho)[e] = vr;
-        const_cast<T *>(d.alpha)[e] = va;
+        d.lam()[e] = vl;
+        d.mu()[e] = vm;
+        d.rho()[e] = vr;
+        d.alpha()[e] = va;
     }
 }
 
 template <typename T>
 hipError_t launch_convert_maps(const Dev<T> &d, const float *lam, const float *mu, const float *rho,
                                const float *alpha, hipStream_t s) {
-    const long long total = d.plane * (d.nz + 4);
+    const long long total = d.plane() * (d.nz + 4);
     hipLaunchKernelGGL(k_convert_maps<T>, dim3(4096), dim3(256), 0, s, d, lam, mu, rho, alpha, total);
     return hipGetLastError();
 }
@@ -124,15 +126,15 @@ __global__ void k_fill(T *p, long long n) {
 
 template <typename T>
 hipError_t launch_zero_state(const Dev<T> &d, hipStream_t s) {
-    const long long n = d.plane * (d.nz + 4);
+    const long long n = d.plane() * (d.nz + 4);
     for (int f = 0; f < NFIELD; ++f) {
-        hipLaunchKernelGGL(k_fill<T>, dim3(2048), dim3(256), 0, s, d.f[f], n);
+        hipLaunchKernelGGL(k_fill<T>, dim3(2048), dim3(256), 0, s, d.f(f), n);
     }
     if (d.P > 0) {
-        const long long ns[3] = {(long long)d.W * d.ny * d.nz, (long long)d.nx * d.W * d.nz,
-                                 (long long)d.nx * d.ny * d.W};
+        const long long ns[3] = {(long long)d.W() * d.ny * d.nz, (long long)d.nx * d.W() * d.nz,
+                                 (long long)d.nx * d.ny * d.W()};
         for (int a = 0; a < 3; ++a)
-            for (int q = 0; q < 6; ++q) hipLaunchKernelGGL(k_fill<T>, dim3(512), dim3(256), 0, s, d.mem[a][q], ns[a]);
+            for (int q = 0; q < 6; ++q) hipLaunchKernelGGL(k_fill<T>, dim3(512), dim3(256), 0, s, d.mem(a, q), ns[a]);
     }
     return hipGetLastError();
 }
@@ -179,8 +181,8 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
     const int x1 = min(x0 + kTileX, d.nx), y1 = min(y0 + kTileY, d.ny), z1 = min(z0 + tl.zc, d.nz);
     int solid = 0, vary = 0;
     const int ax = max(x0 - 2, 0), ay = max(y0 - 2, 0), az = max(z0 - 2, 0);
-    const long long e0 = (long long)(az + 2) * d.plane + (long long)ay * d.px + ax;
-    const T l0 = d.lam[e0], r0 = d.rho[e0], a0 = d.alpha[e0];
+    const long long e0 = (long long)(az + 2) * d.plane() + (long long)ay * d.px() + ax;
+    const T l0 = d.lam()[e0], r0 = d.rho()[e0], a0 = d.alpha()[e0];
     {
         const int w = min(x1 + 2, d.nx) - ax, hgt = min(y1 + 2, d.ny) - ay, dep = min(z1 + 2, d.nz) - az;
         const long long n = (long long)w * hgt * dep;
@@ -188,9 +190,9 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
             const int xx = ax + (int)(e % w);
             const long long rr = e / w;
             const int yy = ay + (int)(rr % hgt), zz = az + (int)(rr / hgt);
-            const long long c = (long long)(zz + 2) * d.plane + (long long)yy * d.px + xx;
-            if (d.mu[c] != T(0)) solid = 1;
-            if (!same_bits(d.lam[c], l0) || !same_bits(d.rho[c], r0) || !same_bits(d.alpha[c], a0)) vary = 1;
+            const long long c = (long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx;
+            if (d.mu()[c] != T(0)) solid = 1;
+            if (!same_bits(d.lam()[c], l0) || !same_bits(d.rho()[c], r0) || !same_bits(d.alpha()[c], a0)) vary = 1;
         }
     }
     solid = __syncthreads_or(solid);
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
         int sol = 0;
         if (xx >= 0 && xx < d.nx && yy >= 0 && yy < d.ny)
             for (int zz = az; zz < min(z1 + 2, d.nz); ++zz)
-                if (d.mu[(long long)(zz + 2) * d.plane + (long long)yy * d.px + xx] != T(0)) sol = 1;
+                if (d.mu()[(long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx] != T(0)) sol = 1;
         col_solid[e] = (unsigned char)sol;
     }
     __syncthreads();
@@ -229,10 +231,10 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
         for (int row = 0; row < kTileY; ++row)
             if (rowm[row]) {
                 const int lane = __ffsll((long long)rowm[row]) - 1;
-                const long long c = (long long)(z0 + 2) * d.plane + (long long)(y0 + row) * d.px + x0 + lane;
-                rl = d.lam[c];
-                rr = d.rho[c];
-                ra = d.alpha[c];
+                const long long c = (long long)(z0 + 2) * d.plane() + (long long)(y0 + row) * d.px() + x0 + lane;
+                rl = d.lam()[c];
+                rr = d.rho()[c];
+                ra = d.alpha()[c];
                 break;
             }
         ref[0] = rl;
@@ -248,8 +250,8 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
         int v = 0;
         if (xx >= 0 && xx < d.nx && yy >= 0 && yy < d.ny)
             for (int zz = az; zz < min(z1 + 2, d.nz); ++zz) {
-                const long long c = (long long)(zz + 2) * d.plane + (long long)yy * d.px + xx;
-                if (!same_bits(d.lam[c], ref[0]) || !same_bits(d.rho[c], ref[1]) || !same_bits(d.alpha[c], ref[2])) v = 1;
+                const long long c = (long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx;
+                if (!same_bits(d.lam()[c], ref[0]) || !same_bits(d.rho()[c], ref[1]) || !same_bits(d.alpha()[c], ref[2])) v = 1;
             }
         col_vary[e] = (unsigned char)v;
     }
@@ -288,7 +290,7 @@ __device__ __forceinline__ long long padded(const Dev<T> &d, long long q) {
     const long long r = q - k * nxy;
     const long long j = r / d.nx;
     const long long i = r - j * d.nx;
-    return (k + 2) * d.plane + j * d.px + i;
+    return (k + 2) * d.plane() + j * d.px() + i;
 }
 
 // tau': s11 = s22 = s33 = -p0/3 (Sec. 3, eq. initialp0); other fields were zeroed.
@@ -297,9 +299,9 @@ __global__ void k_inject(Dev<T> d, const T *p0, long long n) {
     for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < n; q += (long long)gridDim.x * blockDim.x) {
         const T v = -p0[q] / T(3);
         const long long e = padded(d, q);
-        d.f[S11][e] = v;
-        d.f[S22][e] = v;
-        d.f[S33][e] = v;
+        d.f(S11)[e] = v;
+        d.f(S22)[e] = v;
+        d.f(S33)[e] = v;
     }
 }
 
@@ -324,20 +326,36 @@ hipError_t launch_gather(const Dev<T> &d, const Rec &r, double *row, hipStream_t
     return hipGetLastError();
 }
 
-// ctr != null (captured step graphs): y is the whole trace array and the row is *ctr (the
-// adjoint velocity launch before it has stepped the counter back), so one graph of K steps
-// serves every chunk of the time loop.
+// Theta^T y of the first trace row the adjoint takes, added to the zero state; the normal
+// adjoint memory variables, which hold a (b psi~ + dt w) for the coming step, receive a dt times
+// the same increment.
 template <typename T>
-__global__ void k_scatter(Dev<T> d, Rec r, const double *y, const int *ctr) {
+__global__ void k_scatter(Dev<T> d, Rec r, const double *y) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= r.npts) return;
-    scatter_point(d, r, ctr ? y + (size_t)(*ctr) * r.nrec : y, t);
+    const T add = scatter_value<T>(r, y, t);
+    const long long q = r.pt[t];
+    const T kf = T(3) * d.lam()[q] + T(2) * d.mu()[q], dw = add * kf;
+    for (int c = 0; c < 3; ++c) d.f(S11 + c)[q] = fma(add, kf, d.f(S11 + c)[q]);
+    if (d.P <= 0) return;
+    const int crd[3] = {r.ptc[3 * t], r.ptc[3 * t + 1], r.ptc[3 * t + 2]};
+    for (int a = 0; a < 3; ++a) {
+        const int s = slab_own(d, a, crd[a]);
+        if (s >= 0) d.mem(a, 3 + a)[slab_byte(d, a, s, crd[0], crd[1], crd[2]) / sizeof(T)] += (a == 2 ? d.zab(0)[2 * crd[2]] : d.pa(a, 0)[crd[a]]) * d.dt * dw;
+    }
 }
 
 template <typename T>
-hipError_t launch_scatter(const Dev<T> &d, const Rec &r, const double *y, hipStream_t s, const int *ctr) {
+hipError_t launch_scatter(const Dev<T> &d, const Rec &r, const double *y, hipStream_t s) {
     if (r.npts == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter<T>, dim3((r.npts + 255) / 256), dim3(256), 0, s, d, r, y, ctr);
+    hipLaunchKernelGGL(k_scatter<T>, dim3((r.npts + 255) / 256), dim3(256), 0, s, d, r, y);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_zero_inc(const Dev<T> &d, long long n, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fill<T>, dim3((unsigned)std::min<long long>((n + 255) / 256, 2048)), dim3(256), 0, s, d.inc(), n);
     return hipGetLastError();
 }
 
@@ -355,7 +373,7 @@ template <typename T>
 __global__ void k_extract(Dev<T> d, T *out, long long n) {
     for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < n; q += (long long)gridDim.x * blockDim.x) {
         const long long e = padded(d, q);
-        out[q] = -(d.f[S11][e] + d.f[S22][e] + d.f[S33][e]) / (T(3) * (T(3) * d.lam[e] + T(2) * d.mu[e]));
+        out[q] = -(d.f(S11)[e] + d.f(S22)[e] + d.f(S33)[e]) / (T(3) * (T(3) * d.lam()[e] + T(2) * d.mu()[e]));
     }
 }
 template <typename T>
@@ -459,9 +477,9 @@ hipError_t launch_relax_stats(const float *ar, int nx, int ny, int nz, int margi
 template <typename T>
 __global__ void k_relax_map(Dev<T> d, const float *ar, T *dst, long long total) {
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        const long long zp = e / d.plane;
-        const long long rem = e - zp * d.plane;
-        const int y = (int)(rem / d.px), x = (int)(rem - (long long)y * d.px);
+        const long long zp = e / d.plane();
+        const long long rem = e - zp * d.plane();
+        const int y = (int)(rem / d.px()), x = (int)(rem - (long long)y * d.px());
         const int z = (int)zp - 2;
         T v = T(0);
         if (z >= 0 && z <= d.nz && y <= d.ny && x <= d.nx)
@@ -481,13 +499,13 @@ __global__ __launch_bounds__(256) void k_relax_flags(Dev<T> d, Tiles tl, const T
     const int bx = q % tl.ntx, r = q / tl.ntx, by = r % tl.nty, bz = r / tl.nty;
     const int x0 = bx * kTileX, y0 = by * kTileY, z0 = bz * tl.zc;
     const int w = min(kTileX, d.nx - x0), hgt = min(kTileY, d.ny - y0), dep = min(tl.zc, d.nz - z0);
-    const long long stride[3] = {1, d.px, d.plane};
+    const long long stride[3] = {1, d.px(), d.plane()};
     int n = 0;
     for (long long e = threadIdx.x; e < (long long)w * hgt * dep; e += blockDim.x) {
         const int xx = x0 + (int)(e % w);
         const long long rr = e / w;
         const int yy = y0 + (int)(rr % hgt), zz = z0 + (int)(rr / hgt);
-        const long long c = (long long)(zz + 2) * d.plane + (long long)yy * d.px + xx;
+        const long long c = (long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx;
         for (int a = 0; a < 3; ++a)
             if (T(0.5) * (ar[c] + ar[c + stride[a]]) > T(0)) ++n;
     }
@@ -505,7 +523,7 @@ __global__ __launch_bounds__(256) void k_relax_flags(Dev<T> d, Tiles tl, const T
 template <typename T>
 hipError_t launch_relax_setup(const Dev<T> &d, const Tiles &tl, const float *ar_cells, const Relax<T> &r,
                               hipStream_t s) {
-    const long long total = d.plane * (d.nz + 4);
+    const long long total = d.plane() * (d.nz + 4);
     hipLaunchKernelGGL(k_relax_map<T>, dim3(4096), dim3(256), 0, s, d, ar_cells, const_cast<T *>(r.ar), total);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || tl.ntiles == 0) return e;
@@ -527,7 +545,7 @@ __global__ __launch_bounds__(256) void k_relax_compact(Dev<T> d, Tiles tl, Relax
     const int ncell = w * hgt * dep;
     const long long base = r.off[q];
     const int limit = r.count[q];
-    const long long stride[3] = {1, d.px, d.plane};
+    const long long stride[3] = {1, d.px(), d.plane()};
     __shared__ int wave_n[4];
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     int done = 0;
@@ -540,7 +558,7 @@ __global__ __launch_bounds__(256) void k_relax_compact(Dev<T> d, Tiles tl, Relax
             if (e < ncell) {
                 const int xx = x0 + e % w, rem = e / w;
                 const int yy = y0 + rem % hgt, zz = z0 + rem / hgt;
-                el = (long long)(zz + 2) * d.plane + (long long)yy * d.px + xx;
+                el = (long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx;
                 beta = T(0.5) * (r.ar[el] + r.ar[el + stride[c]]);
                 on = beta > T(0);
             }
@@ -565,7 +583,7 @@ __global__ __launch_bounds__(256) void k_relax_compact(Dev<T> d, Tiles tl, Relax
     // the flags kernel counted these points with the same test, so nothing is left; were any
     // left, they become points with beta = 0 (R the identity) on the tile's first cell
     for (int pos = done + (int)threadIdx.x; pos < limit; pos += 256) {
-        r.pts[base + pos] = (unsigned)((long long)(z0 + 2) * d.plane + (long long)y0 * d.px + x0);
+        r.pts[base + pos] = (unsigned)((long long)(z0 + 2) * d.plane() + (long long)y0 * d.px() + x0);
         r.beta[base + pos] = T(0);
     }
 }
@@ -606,7 +624,7 @@ __global__ __launch_bounds__(256) void k_relax(Dev<T> d, Relax<T> r) {
     T z[L];
 #pragma unroll
     for (int l = 0; l < L; ++l) z[l] = r.zeta[l * r.npts + p];
-    T *u = c == 0 ? d.f[U1] : (c == 1 ? d.f[U2] : d.f[U3]);
+    T *u = c == 0 ? d.f(U1) : (c == 1 ? d.f(U2) : d.f(U3));
     const T uo = u[e];
     const T dt = d.dt;
     T bl[L];
@@ -702,7 +720,8 @@ hipError_t launch_dot(const T *a, const T *b, long long n, double *partial, doub
                                            unsigned long long *, hipStream_t);                                       \
     template hipError_t launch_inject<T>(const Dev<T> &, const T *, hipStream_t);                                    \
     template hipError_t launch_gather<T>(const Dev<T> &, const Rec &, double *, hipStream_t);                        \
-    template hipError_t launch_scatter<T>(const Dev<T> &, const Rec &, const double *, hipStream_t, const int *);    \
+    template hipError_t launch_scatter<T>(const Dev<T> &, const Rec &, const double *, hipStream_t);                 \
+    template hipError_t launch_zero_inc<T>(const Dev<T> &, long long, hipStream_t);                                  \
     template hipError_t launch_extract<T>(const Dev<T> &, T *, hipStream_t);                                         \
     template hipError_t launch_dot<T>(const T *, const T *, long long, double *, double *, hipStream_t);           \
     template hipError_t launch_relax_setup<T>(const Dev<T> &, const Tiles &, const float *, const Relax<T> &,      \
