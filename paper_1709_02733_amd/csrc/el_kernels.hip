@@ -54,9 +54,35 @@ hipError_t launch_convert_maps(const Dev<T> &d, const float *lam, const float *m
 // Media statistics in double: [0] max (lambda+2mu)/rho, [1] min rho, [2] min mu, [3] min lambda+2mu,
 // [4] max dt*alpha, [5] min dt*alpha, [6] count of non-finite values, [7] min 3 lambda + 2 mu (three
 // times the bulk modulus).
-__global__ void k_media_stats_partial(const float *lam, const float *mu, const float *rho, const float *alpha,
-                                      long long n, double dt, double *partial) {
-    double v[kStats] = {0.0, INFINITY, INFINITY, INFINITY, -INFINITY, INFINITY, 0.0, INFINITY};
+__device__ __forceinline__ void stats_zero(double (&v)[kStats]) {
+    const double zero[kStats] = {0.0, INFINITY, INFINITY, INFINITY, -INFINITY, INFINITY, 0.0, INFINITY};
+#pragma unroll
+    for (int q = 0; q < kStats; ++q) v[q] = zero[q];
+}
+__device__ __forceinline__ double stats_join(int q, double a, double b) {
+    return q == 0 || q == 4 ? fmax(a, b) : (q == 6 ? a + b : fmin(a, b));
+}
+// The 256 threads' statistics joined into thread 0's.
+__device__ __forceinline__ void stats_block(double (&v)[kStats]) {
+    __shared__ double sh[kStats][4];
+#pragma unroll
+    for (int q = 0; q < kStats; ++q) {
+        for (int m = 32; m >= 1; m >>= 1) v[q] = stats_join(q, v[q], __shfl_xor(v[q], m));
+        if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int q = 0; q < kStats; ++q)
+        for (int w = 1; w < 4; ++w) v[q] = stats_join(q, v[q], sh[q][w]);
+}
+
+// One read of the four maps, bound by memory: 1024 blocks keep enough loads in flight (384^3: 128
+// blocks took 1053 us, these 215 us).
+__global__ __launch_bounds__(256) void k_media_stats_partial(const float *lam, const float *mu, const float *rho,
+                                                             const float *alpha, long long n, double dt, double *partial) {
+    double v[kStats];
+    stats_zero(v);
     for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < n; p += (long long)gridDim.x * blockDim.x) {
         const double l = lam[p], m = mu[p], r = rho[p], a = alpha[p];
         if (!isfinite(l) || !isfinite(m) || !isfinite(r) || !isfinite(a)) v[6] += 1.0;
@@ -69,50 +95,28 @@ __global__ void k_media_stats_partial(const float *lam, const float *mu, const f
         v[5] = fmin(v[5], dt * a);
         v[7] = fmin(v[7], 3.0 * l + 2.0 * m);
     }
-    __shared__ double sh[kStats][256];
-    for (int q = 0; q < kStats; ++q) sh[q][threadIdx.x] = v[q];
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) {
-            const int t = threadIdx.x;
-            sh[0][t] = fmax(sh[0][t], sh[0][t + st]);
-            sh[1][t] = fmin(sh[1][t], sh[1][t + st]);
-            sh[2][t] = fmin(sh[2][t], sh[2][t + st]);
-            sh[3][t] = fmin(sh[3][t], sh[3][t + st]);
-            sh[4][t] = fmax(sh[4][t], sh[4][t + st]);
-            sh[5][t] = fmin(sh[5][t], sh[5][t + st]);
-            sh[6][t] = sh[6][t] + sh[6][t + st];
-            sh[7][t] = fmin(sh[7][t], sh[7][t + st]);
-        }
-        __syncthreads();
-    }
+    stats_block(v);
     if (threadIdx.x == 0)
-        for (int q = 0; q < kStats; ++q) partial[q * kDotBlocks + blockIdx.x] = sh[q][0];
+        for (int q = 0; q < kStats; ++q) partial[q * kDotBlocks + blockIdx.x] = v[q];
 }
 
-__global__ void k_media_stats_final(const double *partial, int nb, double *stats) {
-    if (threadIdx.x != 0) return;
-    double v[kStats] = {0.0, INFINITY, INFINITY, INFINITY, -INFINITY, INFINITY, 0.0, INFINITY};
-    for (int b = 0; b < nb; ++b) {
-        v[0] = fmax(v[0], partial[0 * kDotBlocks + b]);
-        v[1] = fmin(v[1], partial[1 * kDotBlocks + b]);
-        v[2] = fmin(v[2], partial[2 * kDotBlocks + b]);
-        v[3] = fmin(v[3], partial[3 * kDotBlocks + b]);
-        v[4] = fmax(v[4], partial[4 * kDotBlocks + b]);
-        v[5] = fmin(v[5], partial[5 * kDotBlocks + b]);
-        v[6] += partial[6 * kDotBlocks + b];
-        v[7] = fmin(v[7], partial[7 * kDotBlocks + b]);
-    }
-    for (int q = 0; q < kStats; ++q) stats[q] = v[q];
+__global__ __launch_bounds__(256) void k_media_stats_final(const double *partial, int nb, double *stats) {
+    double v[kStats];
+    stats_zero(v);
+    for (int b = threadIdx.x; b < nb; b += 256)
+        for (int q = 0; q < kStats; ++q) v[q] = stats_join(q, v[q], partial[q * kDotBlocks + b]);
+    stats_block(v);
+    if (threadIdx.x == 0)
+        for (int q = 0; q < kStats; ++q) stats[q] = v[q];
 }
 
 hipError_t launch_media_stats(const float *lam, const float *mu, const float *rho, const float *alpha, long long n,
                               double dt, double *stats, double *partial, hipStream_t s) {
-    const int nb = 128;   // partial holds kStats * kDotBlocks doubles
+    const int nb = (int)std::min<long long>(kDotBlocks, (n + 255) / 256);   // partial holds kStats * kDotBlocks doubles
     hipLaunchKernelGGL(k_media_stats_partial, dim3(nb), dim3(256), 0, s, lam, mu, rho, alpha, n, dt, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_media_stats_final, dim3(1), dim3(64), 0, s, partial, nb, stats);
+    hipLaunchKernelGGL(k_media_stats_final, dim3(1), dim3(256), 0, s, partial, nb, stats);
     return hipGetLastError();
 }
 
@@ -124,18 +128,30 @@ __global__ void k_fill(T *p, long long n) {
         p[q] = T(0);
 }
 
+// The wavefields and the memory variables of each axis lie in four stretches of the workspace (equal
+// strides, see Layout), every one a multiple of 16 bytes long: one launch clears them all.  (A
+// launch per array, 27 of them, took 2.5 us each on a small grid, 70 us before the first step.)
+struct Stretches {
+    uint4 *at[4];
+    long long n[4];
+};
+__global__ __launch_bounds__(256) void k_zero(Stretches z) {
+    const uint4 zero = {0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        for (long long q = blockIdx.x * 256ll + threadIdx.x; q < z.n[r]; q += gridDim.x * 256ll) z.at[r][q] = zero;
+}
+
 template <typename T>
 hipError_t launch_zero_state(const Dev<T> &d, hipStream_t s) {
-    const long long n = d.plane() * (d.nz + 4);
-    for (int f = 0; f < NFIELD; ++f) {
-        hipLaunchKernelGGL(k_fill<T>, dim3(2048), dim3(256), 0, s, d.f(f), n);
+    Stretches z = {};
+    long long most = 0;
+    for (int r = 0; r < (d.P > 0 ? 4 : 1); ++r) {
+        z.at[r] = reinterpret_cast<uint4 *>(r == 0 ? d.f(0) : d.mem(r - 1, 0));
+        z.n[r] = (r == 0 ? (long long)NFIELD * d.vstr : 6ll * d.mstr[r - 1]) * 16;   // strides in 256 bytes
+        most = std::max(most, z.n[r]);
     }
-    if (d.P > 0) {
-        const long long ns[3] = {(long long)d.W() * d.ny * d.nz, (long long)d.nx * d.W() * d.nz,
-                                 (long long)d.nx * d.ny * d.W()};
-        for (int a = 0; a < 3; ++a)
-            for (int q = 0; q < 6; ++q) hipLaunchKernelGGL(k_fill<T>, dim3(512), dim3(256), 0, s, d.mem(a, q), ns[a]);
-    }
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<long long>((most + 255) / 256, 4096)), dim3(256), 0, s, z);
     return hipGetLastError();
 }
 
@@ -160,6 +176,10 @@ hipError_t launch_zero_state(const Dev<T> &d, hipStream_t s) {
 // stencil passes then take them from there instead of reading the maps (the box holds every
 // map cell the fluid loops read, the edge-replicated padding included), with the same
 // arithmetic and so the same results.
+//
+// Bound by memory: each column of the box is read once, all four maps together, a second time only
+// where the reference is not the box corner's medium (384^3: 1487 us with a division per cell and
+// three reads, 961 us so).
 template <typename T>
 __device__ __forceinline__ bool same_bits(T a, T b);
 template <>
@@ -178,37 +198,33 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
     if (q >= tl.ntiles) return;
     const int bx = q % tl.ntx, r = q / tl.ntx, by = r % tl.nty, bz = r / tl.nty;
     const int x0 = bx * kTileX, y0 = by * kTileY, z0 = bz * tl.zc;
-    const int x1 = min(x0 + kTileX, d.nx), y1 = min(y0 + kTileY, d.ny), z1 = min(z0 + tl.zc, d.nz);
-    int solid = 0, vary = 0;
-    const int ax = max(x0 - 2, 0), ay = max(y0 - 2, 0), az = max(z0 - 2, 0);
+    const int ax = max(x0 - 2, 0), ay = max(y0 - 2, 0), az = max(z0 - 2, 0), bz1 = min(min(z0 + tl.zc, d.nz) + 2, d.nz);
     const long long e0 = (long long)(az + 2) * d.plane() + (long long)ay * d.px() + ax;
     const T l0 = d.lam()[e0], r0 = d.rho()[e0], a0 = d.alpha()[e0];
-    {
-        const int w = min(x1 + 2, d.nx) - ax, hgt = min(y1 + 2, d.ny) - ay, dep = min(z1 + 2, d.nz) - az;
-        const long long n = (long long)w * hgt * dep;
-        for (long long e = threadIdx.x; e < n; e += blockDim.x) {
-            const int xx = ax + (int)(e % w);
-            const long long rr = e / w;
-            const int yy = ay + (int)(rr % hgt), zz = az + (int)(rr / hgt);
-            const long long c = (long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx;
-            if (d.mu()[c] != T(0)) solid = 1;
-            if (!same_bits(d.lam()[c], l0) || !same_bits(d.rho()[c], r0) || !same_bits(d.alpha()[c], a0)) vary = 1;
+    // columns of the tile and two around it, from z0-2 to z1+1: is mu nonzero anywhere, and do
+    // lambda, rho, alpha differ from the box corner's?  (Columns outside the grid hold nothing the
+    // loops read.)
+    constexpr int HX = kTileX + 4, HY = kTileY + 4;
+    __shared__ unsigned char col_solid[HX * HY], col_vary[HX * HY];
+    int solid = 0, vary = 0;
+    for (int e = threadIdx.x; e < HX * HY; e += kTileX * kTileY) {
+        const int xx = x0 - 2 + e % HX, yy = y0 - 2 + e / HX;
+        int sol = 0, var = 0;
+        if (xx >= 0 && xx < d.nx && yy >= 0 && yy < d.ny) {
+            long long c = (long long)(az + 2) * d.plane() + (long long)yy * d.px() + xx;
+#pragma unroll 4
+            for (int zz = az; zz < bz1; ++zz, c += d.plane()) {
+                if (d.mu()[c] != T(0)) sol = 1;
+                if (!same_bits(d.lam()[c], l0) || !same_bits(d.rho()[c], r0) || !same_bits(d.alpha()[c], a0)) var = 1;
+            }
         }
+        col_solid[e] = (unsigned char)sol;
+        col_vary[e] = (unsigned char)var;
+        solid |= sol;
+        vary |= var;
     }
     solid = __syncthreads_or(solid);
     vary = __syncthreads_or(vary);
-    // columns of the tile and two around it: does mu vanish from z0-2 to z1+1?
-    constexpr int HX = kTileX + 4, HY = kTileY + 4;
-    __shared__ unsigned char col_solid[HX * HY];
-    for (int e = threadIdx.x; e < HX * HY; e += blockDim.x) {
-        const int xx = x0 - 2 + e % HX, yy = y0 - 2 + e / HX;
-        int sol = 0;
-        if (xx >= 0 && xx < d.nx && yy >= 0 && yy < d.ny)
-            for (int zz = az; zz < min(z1 + 2, d.nz); ++zz)
-                if (d.mu()[(long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx] != T(0)) sol = 1;
-        col_solid[e] = (unsigned char)sol;
-    }
-    __syncthreads();
     const int lx = (int)threadIdx.x % kTileX, ly = (int)threadIdx.x / kTileX;
     int colfluid = 0;
     if (x0 + lx < d.nx && y0 + ly < d.ny) {
@@ -242,20 +258,21 @@ __global__ __launch_bounds__(kTileX * kTileY) void k_classify(Dev<T> d, Tiles tl
         ref[2] = ra;
     }
     __syncthreads();
-    // columns of the tile and two around it: are lambda, rho, alpha the reference's from z0-2
-    // to z1+1?  (Columns outside the grid hold nothing the loops read.)
-    __shared__ unsigned char col_vary[HX * HY];
-    for (int e = threadIdx.x; e < HX * HY; e += blockDim.x) {
-        const int xx = x0 - 2 + e % HX, yy = y0 - 2 + e / HX;
-        int v = 0;
-        if (xx >= 0 && xx < d.nx && yy >= 0 && yy < d.ny)
-            for (int zz = az; zz < min(z1 + 2, d.nz); ++zz) {
-                const long long c = (long long)(zz + 2) * d.plane() + (long long)yy * d.px() + xx;
-                if (!same_bits(d.lam()[c], ref[0]) || !same_bits(d.rho()[c], ref[1]) || !same_bits(d.alpha()[c], ref[2])) v = 1;
+    // the same of lambda, rho, alpha against the reference, where it is not the box corner's medium
+    if (vary && !(same_bits(ref[0], l0) && same_bits(ref[1], r0) && same_bits(ref[2], a0))) {
+        for (int e = threadIdx.x; e < HX * HY; e += kTileX * kTileY) {
+            const int xx = x0 - 2 + e % HX, yy = y0 - 2 + e / HX;
+            int v = 0;
+            if (xx >= 0 && xx < d.nx && yy >= 0 && yy < d.ny) {
+                long long c = (long long)(az + 2) * d.plane() + (long long)yy * d.px() + xx;
+#pragma unroll 4
+                for (int zz = az; zz < bz1; ++zz, c += d.plane())
+                    if (!same_bits(d.lam()[c], ref[0]) || !same_bits(d.rho()[c], ref[1]) || !same_bits(d.alpha()[c], ref[2])) v = 1;
             }
-        col_vary[e] = (unsigned char)v;
+            col_vary[e] = (unsigned char)v;
+        }
+        __syncthreads();
     }
-    __syncthreads();
     int colunif = colfluid;
     for (int dy = 0; dy < 5 && colunif; ++dy)
         for (int dx = 0; dx < 5; ++dx)
