@@ -402,31 +402,86 @@ hipError_t launch_extract(const Dev<T> &d, T *p, hipStream_t s) {
 // ---------------------------------------------------- transducer response
 //
 // Every trace (time-major [M][L] doubles) convolved in time with one causal kernel
-// h[0..nh-1], or correlated with it (the adjoint).  One thread per output sample; the
-// lanes of a wavefront cover consecutive receivers, so every load is coalesced, and a
-// block's 64 consecutive time samples share the inputs of their window in L1.
-__global__ void k_eir(const double *h, int nh, const double *in, double *out, int M, int L, int transpose) {
+// h[0..nh-1], or correlated with it (the adjoint).  The lanes of a wavefront cover consecutive
+// receivers, so every load is coalesced; a thread forms R consecutive samples of its receiver.
+//
+// Bound by the loads: with a thread per sample every tap cost a load of 8 bytes per lane for one
+// multiply-add.  Here a window of 2 R - 1 inputs stays in registers and serves R taps of R samples,
+// so a load serves R multiply-adds, and the next R inputs are in flight meanwhile; the taps are
+// scalar loads.  Each sample adds its terms in the order of k, as a loop over k does.  EDGE: some
+// samples or taps of this wavefront lie outside the trace (inputs are read at the nearest sample
+// and their terms left out).
+template <int R, bool TR, bool EDGE>
+__device__ __forceinline__ void eir_samples(const double *h, int nh, const double *in, double *out, int M, int L,
+                                            int l, int m0) {
+    const auto *hk = (const __attribute__((address_space(4))) double *)(unsigned long long)h;
+    const int lane = min(l, L - 1);
+    auto at = [&](int m) { return in[(size_t)(EDGE ? max(0, min(m, M - 1)) : m) * L + lane]; };
+    // taps k0 .. k0 + R - 1 of samples m0 .. m0 + R - 1 take inputs first(k0) .. first(k0) + 2 R - 2
+    auto first = [&](int k0) { return TR ? m0 + k0 : m0 - k0 - (R - 1); };
+    double acc[R] = {}, w[2 * R - 1], next[R];
+#pragma unroll
+    for (int j = 0; j < 2 * R - 1; ++j) w[j] = at(first(0) + j);
+    for (int k0 = 0; k0 < nh; k0 += R) {
+        const bool more = k0 + R < nh;
+        if (more) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) next[j] = at(first(k0 + R) + (TR ? R - 1 : 0) + j);
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            if (k0 + q >= nh) break;
+            const double t = hk[k0 + q];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int m = TR ? m0 + r + k0 + q : m0 + r - k0 - q;
+                const double v = fma(t, w[TR ? r + q : r - q + R - 1], acc[r]);
+                if (!EDGE || (m >= 0 && m < M)) acc[r] = v;
+            }
+        }
+        if (!more) break;
+#pragma unroll
+        for (int j = 0; j < R - 1; ++j) {
+            if (TR) w[j] = w[j + R];
+            else w[2 * R - 2 - j] = w[R - 2 - j];
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) w[(TR ? R - 1 : 0) + j] = next[j];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (l < L && m0 + r < M) out[(size_t)(m0 + r) * L + l] = acc[r];
+}
+template <int R, bool TR>
+__global__ __launch_bounds__(256) void k_eir(const double *h, int nh, const double *in, double *out, int M, int L) {
     const int nlb = (L + 63) / 64;
     const int l = (int)(blockIdx.x % nlb) * 64 + (int)(threadIdx.x & 63);
-    const int m = (int)(blockIdx.x / nlb) * 4 + (int)(threadIdx.x >> 6);
-    if (l >= L || m >= M) return;
-    double acc = 0.0;
-    if (!transpose) {
-        const int kmax = min(m, nh - 1);
-        for (int k = 0; k <= kmax; ++k) acc += h[k] * in[(size_t)(m - k) * L + l];
-    } else {
-        const int kmax = min(M - 1 - m, nh - 1);
-        for (int k = 0; k <= kmax; ++k) acc += h[k] * in[(size_t)(m + k) * L + l];
-    }
-    out[(size_t)m * L + l] = acc;
+    const int m0 = __builtin_amdgcn_readfirstlane(((int)(blockIdx.x / nlb) * 4 + (int)(threadIdx.x >> 6)) * R);
+    if (m0 >= M) return;
+    const int reach = (nh + R - 1) / R * R - 1;   // the furthest tap of the last block of taps
+    const bool inside = m0 + R <= M && (TR ? reach < M - (m0 + R - 1) : reach <= m0);
+    if (inside) eir_samples<R, TR, false>(h, nh, in, out, M, L, l, m0);
+    else eir_samples<R, TR, true>(h, nh, in, out, M, L, l, m0);
 }
 
+template <int R>
+hipError_t launch_eir_r(const double *h, int nh, const double *in, double *out, int M, int L, int transpose,
+                        hipStream_t s) {
+    const long long blocks = (long long)((L + 63) / 64) * ((M + 4 * R - 1) / (4 * R));   // < 2^31 (checked by the caller)
+    if (transpose) hipLaunchKernelGGL((k_eir<R, true>), dim3((unsigned)blocks), dim3(256), 0, s, h, nh, in, out, M, L);
+    else hipLaunchKernelGGL((k_eir<R, false>), dim3((unsigned)blocks), dim3(256), 0, s, h, nh, in, out, M, L);
+    return hipGetLastError();
+}
 hipError_t launch_eir(const double *h, int nh, const double *in, double *out, int M, int L, int transpose,
                       hipStream_t s) {
     if (M == 0 || L == 0) return hipSuccess;
-    const long long blocks = (long long)((L + 63) / 64) * ((M + 3) / 4);   // < 2^31 (checked by the caller)
-    hipLaunchKernelGGL(k_eir, dim3((unsigned)blocks), dim3(256), 0, s, h, nh, in, out, M, L, transpose);
-    return hipGetLastError();
+    // 8 samples per thread where that leaves two wavefronts per SIMD, else 4.  Measured (samples x
+    // receivers, taps; us at one sample per thread as it was, then at 2, 4, 8, 12 and 16):
+    // 2500 x 1024, 171: 213, 124, 75, 45, 55, 59; 3000 x 1024, 400: 538, 349, 171, 97, 98, 120;
+    // 1000 x 512, 171: 48, 29, 22, 24, 38, 49; 2500 x 128, 171: 25, 24, 20, 23, 37, 48.
+    const long long wavefronts = (long long)((L + 63) / 64) * ((M + 7) / 8);
+    if (wavefronts >= 2048) return launch_eir_r<8>(h, nh, in, out, M, L, transpose, s);
+    return launch_eir_r<4>(h, nh, in, out, M, L, transpose, s);
 }
 
 // ------------------------------------------------- frequency-dependent absorption
