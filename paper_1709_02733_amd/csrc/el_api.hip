@@ -172,6 +172,7 @@ Tiles make_tiles(int nx, int ny, int nz) {
         }
     t.cap = (int)*std::max_element(cnt, cnt + 8);
     if (!t.bands()) t.cap = (int)((all + 7) / 8 + 4 * t.run());
+    if (t.boxes(nx, ny)) t.cap = (int)all;   // (a small grid)
     return t;
 }
 
@@ -181,6 +182,15 @@ Tiles make_tiles(int nx, int ny, int nz) {
 // every z band (the same share of the C-PML layers of y and z; every region spans the x extent)
 // and a region's neighbouring tiles share one L2.  Smaller grids deal runs of pieces (index: the
 // piece's number in z-major order) round-robin.
+//
+// Where those regions are slivers, y bands of at most three tile rows on a grid of at most a
+// million cells, each XCD takes one box of equal cost instead (cut_regions): its surface is smaller,
+// so fewer taps miss its L2.  Measured (us per forward / adjoint step, bands and boxes): skull
+// medium 48^3 12.2/12.5 and 11.7/12.1, 64^3 14.1/15.5 and 13.3/14.8, 96^3 26.8/29.5 and 26.6/29.1,
+// 112^3 36.2/39.9 and 36.4/40.5, 128^3 41.8/46.6 and 42.7/47.8, 192^3 116.9/125.7 and 123.1/133.2,
+// 288^3 373/387 and 393/408; soft tissue 64^3 11.0/11.0 and 10.6/10.9, 96^3 17.4/17.8 and
+// 16.8/17.5, 128^3 31.4/33.2 and 32.4/34.0, 208^3 138/144 and 144/151.  On large grids the bands
+// win: every XCD is at the same planes at the same time, and carries the same mix of updates.
 int piece_xcd(const Tiles &t, int by, int z, long long index) {
     if (t.bands()) return (by * 8 / t.nty + z * 8 / t.nz) % 8;
     return (int)(index / t.run() % 8);
@@ -197,6 +207,106 @@ unsigned tile_edges(const Tiles &t, const unsigned char *fast, int q) {
         if (b[a] + 1 < nb[a] && !fast[q + step[a]]) edges |= 1u << (2 * a + 1);
     }
     return edges;
+}
+
+// What the regions are cut by: the cost of a sub-tile's general update, of the layers of an axis
+// (both in units of a fluid sub-tile), and how uneven a cut may be.
+constexpr double kGeneralCost = 2.0, kLayerCost = 0.3, kEvenCut = 0.02;
+// Regions of equal cost, one per XCD: boxes of tile columns and planes, by cutting the grid, then
+// each part, at the point of its longest axis that halves its cost; another axis where that one's
+// whole tiles (columns of cells) would leave the halves uneven.
+struct Region {
+    int b[3], e[3];   // tiles along x and y, planes
+};
+void cut_regions(const Tiles &t, const std::vector<float> &cost, Region box, int parts, Region *out) {
+    if (parts == 1) {
+        *out = box;
+        return;
+    }
+    std::vector<double> along[3];
+    for (int a = 0; a < 3; ++a) along[a].assign(box.e[a] - box.b[a], 0.0);
+    for (int z = box.b[2]; z < box.e[2];) {
+        const int bz = z / t.zc, z1 = std::min((bz + 1) * t.zc, box.e[2]);
+        double plane = 0;
+        for (int by = box.b[1]; by < box.e[1]; ++by) {
+            const float *row = &cost[((size_t)bz * t.nty + by) * t.ntx];
+            double sum = 0;
+            for (int bx = box.b[0]; bx < box.e[0]; ++bx) {
+                along[0][bx - box.b[0]] += row[bx] * (z1 - z);
+                sum += row[bx];
+            }
+            along[1][by - box.b[1]] += sum * (z1 - z);
+            plane += sum;
+        }
+        for (; z < z1; ++z) along[2][z - box.b[2]] = plane;
+    }
+    double total = 0;
+    for (double c : along[0]) total += c;
+    const int unit[3] = {kTileX, kTileY, 1};
+    int axis = -1, at = 0;
+    double best = 0;
+    for (int a = 2; a >= 0; --a) {
+        const int n = box.e[a] - box.b[a];
+        if (n < 2) continue;
+        double left = 0, off = 1;
+        int cut = 1;
+        for (int c = 1; c < n; ++c) {
+            left += along[a][c - 1];
+            const double o = std::fabs(left / total - 0.5);
+            if (o < off) {
+                off = o;
+                cut = c;
+            }
+        }
+        const double score = off <= kEvenCut ? (double)n * unit[a] : -off;
+        if (axis < 0 || score > best) {
+            axis = a;
+            at = cut;
+            best = score;
+        }
+    }
+    if (axis < 0) {   // one tile of one plane: nothing to share out
+        out[0] = box;
+        for (int q = 1; q < parts; ++q) out[q] = Region{{0, 0, 0}, {0, 0, 0}};
+        return;
+    }
+    Region lo = box, hi = box;
+    lo.e[axis] = hi.b[axis] = box.b[axis] + at;
+    cut_regions(t, cost, lo, parts / 2, out);
+    cut_regions(t, cost, hi, parts / 2, out + parts / 2);
+}
+// Cost of a tile's chunk per plane, in sub-tiles of the fluid update.
+std::vector<float> chunk_costs(const Tiles &t, int nx, int ny, int P, const unsigned char *fast,
+                               const unsigned long long *lanes) {
+    std::vector<float> cost(t.ntiles);
+    auto layers = [P](int c0, int c1, int n) { return P <= 0 ? 0 : std::max(0, std::min(c1, P) - c0) + std::max(0, c1 - std::max(c0, n - P)); };
+    int q = 0;
+    for (int bz = 0; bz < t.nzc; ++bz) {
+        const int z0 = bz * t.zc, z1 = std::min(z0 + t.zc, t.nz);
+        const float lz = (float)kLayerCost * layers(z0, z1, t.nz) / (float)(z1 - z0);
+        for (int by = 0; by < t.nty; ++by) {
+            const int y0 = by * kTileY, y1 = std::min(y0 + kTileY, ny);
+            const float ly = (float)kLayerCost * layers(y0, y1, ny) / (float)(y1 - y0);
+            for (int bx = 0; bx < t.ntx; ++bx, ++q) {
+                const int x0 = bx * kTileX, x1 = std::min(x0 + kTileX, nx);
+                float c = 0;   // sub-tiles
+                for (int s = 0; s < 4; ++s) {
+                    const int sx = x0 + (s & 1) * kWaveX, sy = y0 + (s >> 1) * kWaveY;
+                    if (sx >= nx || sy >= ny) continue;
+                    bool fluid = fast && fast[q];
+                    if (fast && !fluid) {
+                        const unsigned valid = nx - sx >= kWaveX ? ~0u : (1u << (nx - sx)) - 1;
+                        fluid = true;
+                        for (int r = 0; r < kWaveY && sy + r < ny; ++r)
+                            fluid = fluid && ((unsigned)(lanes[(size_t)kTileY * q + (s >> 1) * kWaveY + r] >> ((s & 1) * kWaveX)) & valid) == valid;
+                    }
+                    c += fluid ? 1.f : (float)kGeneralCost;
+                }
+                cost[q] = c * (1.f + lz + ly + (float)kLayerCost * layers(x0, x1, nx) / (float)(x1 - x0));
+            }
+        }
+    }
+    return cost;
 }
 
 // Do chunks q and q + step of a tile column (one above the other) ask for the same update?
@@ -221,7 +331,7 @@ bool same_update(const Tiles &t, const unsigned char *fast, const unsigned char 
 }
 
 template <typename T>
-BlockList<T> block_list(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned char *uni,
+BlockList<T> block_list(const Tiles &t, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
                         const unsigned long long *lanes, const T *med, const std::vector<int> &points) {
     // room for cap entries per XCD (an entry costs its 64 bytes only once it is written)
     BlockList<T> out;
@@ -234,6 +344,17 @@ BlockList<T> block_list(const Tiles &t, int nx, int ny, const unsigned char *fas
     };
     std::vector<Run> runs((size_t)t.ntx * t.nty, Run{0, 0, 0});
     const int step = t.ntx * t.nty;
+    Region region[8] = {};
+    const bool boxed = t.boxes(nx, ny);
+    if (boxed) cut_regions(t, chunk_costs(t, nx, ny, npml, fast, lanes), Region{{0, 0, 0}, {t.ntx, t.nty, t.nz}}, 8, region);
+    auto xcd_of = [&](int bx, int by, int z, long long index) {
+        if (boxed)
+            for (int x = 0; x < 8; ++x) {
+                const Region &g = region[x];
+                if (bx >= g.b[0] && bx < g.e[0] && by >= g.b[1] && by < g.e[1] && z >= g.b[2] && z < g.e[2]) return x;
+            }
+        return piece_xcd(t, by, z, index);
+    };
     // with scatter points: the pieces (entries at first, first + 8, ..., n of them; their sub-tiles
     // with points; the first one's first increment plane), and per column and plane, 1 + the number
     // of the piece that begins there
@@ -263,7 +384,7 @@ BlockList<T> block_list(const Tiles &t, int nx, int ny, const unsigned char *fas
                 int cut = (z + t.shortest() + t.zb - 1) / t.zb * t.zb;
                 if (run.z1 - cut < (z == run.z0 ? t.shortest() : 2)) cut = run.z1;
                 run.next = cut;
-                const int x = piece_xcd(t, by, z, pieces++);
+                const int x = xcd_of(bx, by, z, pieces++);
                 const size_t first = count[x];
                 BlockEnt<T> e = {bx, by, z, cut, 0, -1, {}, {}, med[4 * (size_t)q], med[4 * (size_t)q + 1], med[4 * (size_t)q + 2]};
                 unsigned in = 0, fl = 0, un = 0;   // sub-tiles with columns in the grid; those all fluid; those all uniform
@@ -638,7 +759,7 @@ el_status set_tables_t(el_plan p, Dev<T> &d, hipStream_t s) {
     p->rec.pos = reinterpret_cast<int *>(ws + p->L.csr_pos[on]);
     p->tiles.order = ws + p->L.tile_order[on];
     if (p->per[on] == 0 && p->tiles.ntiles > 0) {
-        const BlockList<T> list = block_list<T>(p->tiles, p->g.nx, p->g.ny, fast, p->uni.data(), p->lanes.data(),
+        const BlockList<T> list = block_list<T>(p->tiles, p->g.nx, p->g.ny, p->g.npml, fast, p->uni.data(), p->lanes.data(),
                                                 reinterpret_cast<const T *>(p->med.data()), p->points);
         HIP_TRY(hipMemcpyAsync(ws + p->L.tile_order[on], list.entries.get(), 8 * (size_t)list.per * sizeof(BlockEnt<T>),
                                hipMemcpyHostToDevice, s), "block list");

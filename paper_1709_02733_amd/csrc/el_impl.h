@@ -167,6 +167,7 @@ struct Tiles {
     int shortest() const { return zb < 3 ? 2 : zb - 1; }   // planes of a block, unless its run has fewer; s33's bands have two
     int longest() const { return 2 * shortest() + zb - 2; }
     bool bands() const { return nty >= 8 && nz >= 8 * zb; }                 // see piece_xcd
+    bool boxes(int nx, int ny) const { return bands() && nty <= 24 && (long long)nx * ny * nz <= 1 << 20; }
     int run() const { return (int)(((long long)ntx * nty * ((nz + zb - 1) / zb) + 511) / 512); }
     int ntiles;              // ntx * nty * nzc
     int cap;                 // entries per XCD at most
@@ -189,7 +190,7 @@ struct BlockList {
     std::vector<int> pos;    // each point's element in them
 };
 template <typename T>
-BlockList<T> block_list(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned char *uni,
+BlockList<T> block_list(const Tiles &t, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
                         const unsigned long long *lanes, const T *med, const std::vector<int> &points);
 // Faces of fluid tile q shared with tiles that are not fluid: bits 0, 1 along y, 2, 3 along z
 // (lower, upper); 0 unless q is a fluid tile.
