@@ -123,7 +123,7 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
 // general update, whose sums round differently from the fluid update's.  How many planes a block
 // updates is another matter (block_planes): the blocks of block_list() cover any run of planes
 // over which a tile column's chunks ask for the same update.
-constexpr int kZChunk = 6;
+constexpr int kZChunk = 6, kZBlock = 4;
 constexpr long long kMinTiles = 4096;
 constexpr int kMaxTiles = (1 << 24) - 1;   // (arrays below 4 GiB keep under it)
 int chunk_planes(int nx, int ny, int nz) {
@@ -132,29 +132,12 @@ int chunk_planes(int nx, int ny, int nz) {
     while (zc > 2 && cols * ((nz + zc - 1) / zc) < kMinTiles) --zc;
     return std::min(zc, nz);
 }
-// Planes per block.  A long column of planes reads fewer halo planes, a short one gives more
-// wavefronts and a shorter chain of planes per wavefront.  Measured with chunks and blocks of the
-// same depth (skull medium, forward / adjoint us per step, 2, 3, 4 and 6 planes): 64^3 14.8/16.3,
-// 15.4/16.0, 16.5/16.8, 19.5/19.1; 96^3 27.7/31.4, 25.8/29.7, 27.6/29.8, 26.7/32.7; 128^3
-// 43.0/49.6, 41.9/46.4, 43.1/46.7, 45.2/48.7; 192^3 120/140, 115/129, 115/126, 118/126; 256^3
-// 285/336, 274/304, 277/295, 281/295; 384^3 800/935, 795/854, 798/831, 804/831.  So 4 planes, 3
-// where that leaves under 4096 blocks of a tile (128^3 and less), and 2 where even 3 leave under
-// 1024 (64^3).
-constexpr int kZBlock = 4;
-constexpr long long kFewTiles = 4096, kVeryFewTiles = 1024;
-int block_planes(int nx, int ny, int nz) {
-    const long long cols = (long long)((nx + kTileX - 1) / kTileX) * ((ny + kTileY - 1) / kTileY);
-    int zb = kZBlock;
-    if (cols * ((nz + zb - 1) / zb) < kFewTiles) --zb;
-    if (zb < kZBlock && cols * ((nz + zb - 1) / zb) < kVeryFewTiles) --zb;
-    return zb;
-}
 Tiles make_tiles(int nx, int ny, int nz) {
     Tiles t;
     t.ntx = (nx + kTileX - 1) / kTileX;
     t.nty = (ny + kTileY - 1) / kTileY;
     t.zc = chunk_planes(nx, ny, nz);
-    t.zb = block_planes(nx, ny, nz);
+    t.zb = kZBlock;
     t.nz = nz;
     t.nzc = (nz + t.zc - 1) / t.zc;
     t.ntiles = t.ntx * t.nty * t.nzc;
@@ -212,6 +195,62 @@ unsigned tile_edges(const Tiles &t, const unsigned char *fast, int q) {
 // What the regions are cut by: the cost of a sub-tile's general update, of the layers of an axis
 // (both in units of a fluid sub-tile), and how uneven a cut may be.
 constexpr double kGeneralCost = 2.0, kLayerCost = 0.3, kEvenCut = 0.02;
+// The sub-tiles of a tile: those with columns in the grid, of these those whose columns are all fluid
+// and those whose columns are all uniform; per sub-tile and row, its fluid and uniform columns (of a
+// tile that is not fluid).
+struct Subs {
+    unsigned in = 0, fluid = 0, same = 0;
+    unsigned cols[4][kWaveY] = {}, uniform[4][kWaveY] = {};
+    int entries() const { return __builtin_popcount(in & ~fluid) + (fluid ? 1 : 0); }
+};
+Subs subs_of(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes, int bx, int by, int q) {
+    Subs u;
+    for (int s = 0; s < 4; ++s) {
+        const int x0 = bx * kTileX + (s & 1) * kWaveX, y0 = by * kTileY + (s >> 1) * kWaveY;
+        if (x0 >= nx || y0 >= ny) continue;
+        u.in |= 1u << s;
+        if (!fast) continue;
+        bool all = true, same = true;
+        if (!fast[q]) {
+            const unsigned valid = nx - x0 >= kWaveX ? ~0u : (1u << (nx - x0)) - 1;
+            for (int r = 0; r < kWaveY && y0 + r < ny; ++r) {
+                const size_t row = (size_t)kTileY * q + (s >> 1) * kWaveY + r;
+                u.cols[s][r] = (unsigned)(lanes[row] >> ((s & 1) * kWaveX)) & valid;
+                u.uniform[s][r] = (unsigned)(lanes[(size_t)kTileY * t.ntiles + row] >> ((s & 1) * kWaveX)) & valid;
+                all = all && u.cols[s][r] == valid;
+                same = same && u.uniform[s][r] == valid;
+            }
+        }
+        if (all) u.fluid |= 1u << s;
+        if (all && same) u.same |= 1u << s;
+    }
+    return u;
+}
+
+// Planes per block.  A long column of planes reads fewer halo planes, a short one gives more
+// wavefronts and a shorter chain of planes per wavefront: kZBlock, two where that leaves few blocks.
+// Measured (us per forward / adjoint step, blocks of 2, 3 and 4 planes; blocks of 4 planes there
+// are): skull medium 64^3 (900) 13.5/14.8, 14.6/15.4, 16.7/17.3; 96^3 (2800)
+// 26.6/29.6, 27.4/29.4, 32.9/35.1; 128^3 (5000) 42.3/47.2, 43.2/47.8, 44.4/48.5; 136^3 (6700)
+// 47.3/51.8, 48.9/52.2, 48.0/51.5; 152^3 (8700) 60.3/70.3, 56.4/61.9, 56.1/59.5; 192^3 124/140, 118/130,
+// 116/124; 384^3 815/909, 804/841, 803/831 (6 planes 807/836); soft tissue 112^3 24.0/25.9,
+// 25.9/27.5, 24.4/25.9; 144^3 (3888) 41.6/44.1, 42.8/44.8, 43.2/44.8; all solid 48^3 13.0/13.4,
+// 13.4/13.7, 15.0/15.1; 80^3 (3200) 26.3/28.3, 25.9/27.6, 26.6/27.6; 112^3 (6272) 50.2/56.7,
+// 50.0/53.9, 48.5/52.6; 128^3 skull in double precision 77.5/92.3, 79.2/93.8, 79.6/95.1.
+constexpr long long kFewBlocks = 5120;
+int block_planes(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes) {
+    long long planes = 0;   // over the entries
+    int q = 0;
+    for (int bz = 0; bz < t.nzc; ++bz) {
+        const int depth = std::min(t.zc, t.nz - bz * t.zc);
+        for (int by = 0; by < t.nty; ++by)
+            for (int bx = 0; bx < t.ntx; ++bx, ++q)
+                planes += (fast && fast[q] ? 1 : subs_of(t, nx, ny, fast, lanes, bx, by, q).entries()) * depth;
+        if (planes >= kFewBlocks * kZBlock) return kZBlock;
+    }
+    return 2;
+}
+
 // Regions of equal cost, one per XCD: boxes of tile columns and planes, by cutting the grid, then
 // each part, at the point of its longest axis that halves its cost; another axis where that one's
 // whole tiles (columns of cells) would leave the halves uneven.
@@ -289,19 +328,8 @@ std::vector<float> chunk_costs(const Tiles &t, int nx, int ny, int P, const unsi
             const float ly = (float)kLayerCost * layers(y0, y1, ny) / (float)(y1 - y0);
             for (int bx = 0; bx < t.ntx; ++bx, ++q) {
                 const int x0 = bx * kTileX, x1 = std::min(x0 + kTileX, nx);
-                float c = 0;   // sub-tiles
-                for (int s = 0; s < 4; ++s) {
-                    const int sx = x0 + (s & 1) * kWaveX, sy = y0 + (s >> 1) * kWaveY;
-                    if (sx >= nx || sy >= ny) continue;
-                    bool fluid = fast && fast[q];
-                    if (fast && !fluid) {
-                        const unsigned valid = nx - sx >= kWaveX ? ~0u : (1u << (nx - sx)) - 1;
-                        fluid = true;
-                        for (int r = 0; r < kWaveY && sy + r < ny; ++r)
-                            fluid = fluid && ((unsigned)(lanes[(size_t)kTileY * q + (s >> 1) * kWaveY + r] >> ((s & 1) * kWaveX)) & valid) == valid;
-                    }
-                    c += fluid ? 1.f : (float)kGeneralCost;
-                }
+                const Subs u = subs_of(t, nx, ny, fast, lanes, bx, by, q);
+                const float c = __builtin_popcount(u.fluid) + (float)kGeneralCost * __builtin_popcount(u.in & ~u.fluid);
                 cost[q] = c * (1.f + lz + ly + (float)kLayerCost * layers(x0, x1, nx) / (float)(x1 - x0));
             }
         }
@@ -331,8 +359,10 @@ bool same_update(const Tiles &t, const unsigned char *fast, const unsigned char 
 }
 
 template <typename T>
-BlockList<T> block_list(const Tiles &t, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
+BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
                         const unsigned long long *lanes, const T *med, const std::vector<int> &points) {
+    Tiles t = tiles;
+    t.zb = block_planes(t, nx, ny, fast, lanes);
     // room for cap entries per XCD (an entry costs its 64 bytes only once it is written)
     BlockList<T> out;
     out.entries.reset(new BlockEnt<T>[8 * (size_t)t.cap]);
@@ -387,25 +417,7 @@ BlockList<T> block_list(const Tiles &t, int nx, int ny, int npml, const unsigned
                 const int x = xcd_of(bx, by, z, pieces++);
                 const size_t first = count[x];
                 BlockEnt<T> e = {bx, by, z, cut, 0, -1, {}, {}, med[4 * (size_t)q], med[4 * (size_t)q + 1], med[4 * (size_t)q + 2]};
-                unsigned in = 0, fl = 0, un = 0;   // sub-tiles with columns in the grid; those all fluid; those all uniform
-                unsigned fluid[4][kWaveY] = {}, uniform[4][kWaveY] = {};
-                for (int s = 0; s < 4; ++s) {
-                    const int x0 = bx * kTileX + (s & 1) * kWaveX, y0 = by * kTileY + (s >> 1) * kWaveY;
-                    if (x0 >= nx || y0 >= ny) continue;
-                    in |= 1u << s;
-                    if (!fast || fast[q]) continue;
-                    const unsigned valid = nx - x0 >= kWaveX ? ~0u : (1u << (nx - x0)) - 1;
-                    bool all = true, same = true;
-                    for (int r = 0; r < kWaveY && y0 + r < ny; ++r) {
-                        const size_t row = (size_t)kTileY * q + (s >> 1) * kWaveY + r;
-                        fluid[s][r] = (unsigned)(lanes[row] >> ((s & 1) * kWaveX)) & valid;
-                        uniform[s][r] = (unsigned)(lanes[(size_t)kTileY * t.ntiles + row] >> ((s & 1) * kWaveX)) & valid;
-                        all = all && fluid[s][r] == valid;
-                        same = same && uniform[s][r] == valid;
-                    }
-                    if (all) fl |= 1u << s;
-                    if (all && same) un |= 1u << s;
-                }
+                const Subs u = subs_of(t, nx, ny, fast, lanes, bx, by, q);
                 auto put = [&](unsigned flags) {
                     e.flags = flags | (count[x] == first ? kBlkFirst : 0u);
                     order[8 * count[x]++ + x] = e;
@@ -414,17 +426,17 @@ BlockList<T> block_list(const Tiles &t, int nx, int ny, int npml, const unsigned
                     unsigned edges = tile_edges(t, fast, q) & 3u;
                     if (e.z0 == run.z0) edges |= tile_edges(t, fast, q) & 4u;
                     if (e.z1 == run.z1) edges |= tile_edges(t, fast, q + ((run.z1 - 1) / t.zc - bz) * step) & 8u;
-                    put(kBlkFast | in << kBlkMaskShift | (uni[q] ? in << kBlkUniShift : 0u) | edges << kBlkEdgeShift);
+                    put(kBlkFast | u.in << kBlkMaskShift | (uni[q] ? u.in << kBlkUniShift : 0u) | edges << kBlkEdgeShift);
                 } else {
                     for (int s = 0; s < 4; ++s) {
-                        if (!((in & ~fl) >> s & 1u)) continue;
+                        if (!((u.in & ~u.fluid) >> s & 1u)) continue;
                         for (int r = 0; r < kWaveY; ++r) {
-                            e.fluid[r] = fluid[s][r];
-                            e.uniform[r] = uniform[s][r];
+                            e.fluid[r] = u.cols[s][r];
+                            e.uniform[r] = u.uniform[s][r];
                         }
                         put(kBlkGen | (unsigned)s << kBlkSubShift);
                     }
-                    if (fl) put(kBlkKeep | fl << kBlkMaskShift | un << kBlkUniShift);
+                    if (u.fluid) put(kBlkKeep | u.fluid << kBlkMaskShift | u.same << kBlkUniShift);
                 }
                 if (points.empty()) continue;
                 piece.push_back({8 * first + x, (int)(count[x] - first), z, cut, 0u, 0});

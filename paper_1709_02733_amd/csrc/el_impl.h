@@ -163,7 +163,7 @@ constexpr unsigned kBlkFast = 1u << 18;
 constexpr int kBlkIncShift = 20;
 struct Tiles {
     int ntx, nty, nzc, zc;   // tiles along x and y, z chunks, planes per chunk
-    int nz, zb;              // planes, planes per block
+    int nz, zb;              // planes, planes per block (at most; block_list may take fewer)
     int shortest() const { return zb < 3 ? 2 : zb - 1; }   // planes of a block, unless its run has fewer; s33's bands have two
     int longest() const { return 2 * shortest() + zb - 2; }
     bool bands() const { return nty >= 8 && nz >= 8 * zb; }                 // see piece_xcd
