@@ -95,7 +95,7 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
     {
         const Tiles t = make_tiles(g.nx, g.ny, g.nz);
         // increments: the planes of a sub-tile's piece with points, at most every plane there is
-        const size_t planes = std::min(E * t.longest(), (size_t)4 * t.ntx * t.nty * g.nz);
+        const size_t planes = std::min(E * Tiles::longest(kZDeep), (size_t)4 * t.ntx * t.nty * g.nz);
         for (size_t &o : L->csr_pos) o = take(E * 4);
         for (size_t &o : L->inc) o = take(planes * kWaveX * kWaveY * es);
         for (size_t &o : L->tile_order) o = take((size_t)8 * t.cap * sizeof(BlockEnt<double>));
@@ -228,7 +228,8 @@ Subs subs_of(const Tiles &t, int nx, int ny, const unsigned char *fast, const un
 }
 
 // Planes per block.  A long column of planes reads fewer halo planes, a short one gives more
-// wavefronts and a shorter chain of planes per wavefront: kZBlock, two where that leaves few blocks.
+// wavefronts and a shorter chain of planes per wavefront: kZBlock, two where that leaves few blocks,
+// kZDeep on large grids that are mostly solid, whose six stresses cost more halo.
 // Measured (us per forward / adjoint step, blocks of 2, 3 and 4 planes; blocks of 4 planes there
 // are): skull medium 64^3 (900) 13.5/14.8, 14.6/15.4, 16.7/17.3; 96^3 (2800)
 // 26.6/29.6, 27.4/29.4, 32.9/35.1; 128^3 (5000) 42.3/47.2, 43.2/47.8, 44.4/48.5; 136^3 (6700)
@@ -237,18 +238,32 @@ Subs subs_of(const Tiles &t, int nx, int ny, const unsigned char *fast, const un
 // 25.9/27.5, 24.4/25.9; 144^3 (3888) 41.6/44.1, 42.8/44.8, 43.2/44.8; all solid 48^3 13.0/13.4,
 // 13.4/13.7, 15.0/15.1; 80^3 (3200) 26.3/28.3, 25.9/27.6, 26.6/27.6; 112^3 (6272) 50.2/56.7,
 // 50.0/53.9, 48.5/52.6; 128^3 skull in double precision 77.5/92.3, 79.2/93.8, 79.6/95.1.
-constexpr long long kFewBlocks = 5120;
+// Mostly solid, 4, 6, 8 and 12 planes: 157 x 131 x 109 (5500 blocks of 8) 65.2/70.5, 68.2/72.8,
+// 67.6/73.6, 76.4/80.3; 203 x 187 x 150 (14288) 223/251, 222/251, 220/250, 225/254; 256^3 564/611,
+// 554/601, 558/601, 561/605; 384^3 1760/1886, 1731/1846, 1721/1829, 1719/1823; 192^3 in double
+// precision (13824) 545/612, 534/599, 532/596, 540/598.
+constexpr long long kFewBlocks = 5120, kManyBlocks = 10240;
 int block_planes(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes) {
-    long long planes = 0;   // over the entries
+    long long planes = 0;        // over the entries
+    long long subs = 0, general = 0;   // sub-tiles
     int q = 0;
     for (int bz = 0; bz < t.nzc; ++bz) {
         const int depth = std::min(t.zc, t.nz - bz * t.zc);
         for (int by = 0; by < t.nty; ++by)
-            for (int bx = 0; bx < t.ntx; ++bx, ++q)
-                planes += (fast && fast[q] ? 1 : subs_of(t, nx, ny, fast, lanes, bx, by, q).entries()) * depth;
-        if (planes >= kFewBlocks * kZBlock) return kZBlock;
+            for (int bx = 0; bx < t.ntx; ++bx, ++q) {
+                if (fast && fast[q]) {
+                    planes += depth;
+                    subs += 4;
+                    continue;
+                }
+                const Subs u = subs_of(t, nx, ny, fast, lanes, bx, by, q);
+                planes += u.entries() * depth;
+                subs += __builtin_popcount(u.in);
+                general += __builtin_popcount(u.in & ~u.fluid);
+            }
     }
-    return 2;
+    if (planes < kFewBlocks * kZBlock) return 2;
+    return 4 * general >= 3 * subs && planes >= kManyBlocks * kZDeep ? kZDeep : kZBlock;
 }
 
 // Regions of equal cost, one per XCD: boxes of tile columns and planes, by cutting the grid, then
