@@ -143,13 +143,14 @@ Tiles make_tiles(int nx, int ny, int nz) {
     t.ntiles = t.ntx * t.nty * t.nzc;
     t.order = nullptr;
     t.per = t.cap = 0;
-    // an XCD's entries at most: four per piece, the pieces of a tile column at least two planes
-    // apart but for a last one
+    // an XCD's entries at most: four per piece.  The pieces of a tile column are at least two planes
+    // apart but for a last one; with chunks of kZChunk planes (and so blocks of kZBlock at least) a
+    // run of D planes has at most (D + 1) / 3, seven in 18 planes
     long long cnt[8] = {}, all = 0;
     for (int by = 0; by < t.nty; ++by)
         for (int z0 = 0, z1 = 0; z0 < nz; z0 = z1) {
             for (z1 = z0 + 1; z1 < nz && z1 * 8 / nz == z0 * 8 / nz; ++z1) {}
-            const int n = 4 * t.ntx * ((z1 - z0 + 1) / 2 + 1);
+            const int n = 4 * t.ntx * (t.zc == kZChunk ? 7 * (z1 - z0) / 18 + 2 : (z1 - z0 + 1) / 2 + 1);
             cnt[piece_xcd(t, by, z0, 0)] += n;
             all += n;
         }
