@@ -130,8 +130,8 @@ constexpr int kWaveX = 32;
 constexpr int kWaveY = 2;
 // An entry of the block list: planes of a tile column and what its block does there.
 // A general entry (kBlkGen) updates one sub-tile (kBlkSubShift), a wavefront per velocity
-// component or per kind of stress.  A fluid entry updates the fluid sub-tiles set in the four bits from kBlkMaskShift, a wavefront
-// each; those also set from kBlkUniShift have uniform lambda, rho and alpha (k_classify), taken
+// component or per kind of stress.  A fluid entry updates the fluid sub-tiles set in the four bits
+// from kBlkMaskShift, a wavefront each; those also set from kBlkUniShift have uniform lambda, rho and alpha (k_classify), taken
 // from a per-tile table instead of the maps.  The general update differences s22 only along y and
 // s33 only along z, with taps reaching two cells into a neighbouring tile, so a fluid tile stores
 // s22 only on two-row bands along the y faces (bits 0, 1 from kBlkEdgeShift: lower, upper) and
@@ -281,8 +281,7 @@ __device__ __forceinline__ void scatter_block(const Dev<T> &d, const Rec &r, con
 inline int scatter_blocks(int npts) { return (npts + 255) / 256; }
 
 // Arguments of a stencil launch over the tiles of G plans of one precision (G = 1: a plan's
-// own forward passes; G = kGroupMax: the grouped passes of el_group, and a plan's own
-// adjoint passes as one member).  Member q owns blocks first[q] .. first[q+1]-1; each
+// own passes; G = kGroupMax: the grouped passes of el_group).  Member q owns blocks first[q] .. first[q+1]-1; each
 // first[q] is a multiple of 8, so that the member's block b - first[q] runs on XCD
 // (b - first[q]) % 8 as its tile order assumes.  Entries past the last member repeat the
 // total block count (or lie beyond every block).  row[q]: the trace row that member's gather

@@ -62,10 +62,12 @@
 // one 64-byte line, and the layer coefficients are loaded without a branch.  A wavefront's
 // scalar registers limit how many fit, too: at most 80 for 8 per SIMD, 96 for 7.
 //
-// Measured (MI355X, us per forward and adjoint step together, before the split and after; "adjoint":
-// that step alone): skull medium 64^3 42.1 to 29.5, 96^3 adjoint 41.9 to 30.7, 128^3 101.0 to 90.7,
-// 128^3 in double precision 196 to 173, 256^3 636 to 567, 384^3 1625 to 1620; 157 x 131 x 109 all
-// solid 141 to 138.
+// Measured (MI355X, us per forward and adjoint step together, with a wavefront per sub-tile and now;
+// "adjoint": that step alone): skull medium 64^3 42.1 to 27.7, 96^3 adjoint 41.9 to 29.6, 128^3
+// 101.9 to 89.4, 128^3 in double precision 197 to 169, 256^3 636 to 565, 384^3 1639 to 1635;
+// all solid 157 x 131 x 109 141 to 137, 203 x 187 x 150 549 to 471, 256^3 1188 to 1158, but 384^3
+// 3472 to 3555, where the passes are bound by memory and a sub-tile's y halo is no longer shared
+// in L1 with the tile's other sub-tiles.
 #include "el_impl.h"
 
 namespace el {
