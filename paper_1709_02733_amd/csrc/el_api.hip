@@ -123,7 +123,7 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
 // general update, whose sums round differently from the fluid update's.  How many planes a block
 // updates is another matter (block_planes): the blocks of block_list() cover any run of planes
 // over which a tile column's chunks ask for the same update.
-constexpr int kZChunk = 6, kZBlock = 4;
+constexpr int kZChunk = 6;
 constexpr long long kMinTiles = 4096;
 constexpr int kMaxTiles = (1 << 24) - 1;   // (arrays below 4 GiB keep under it)
 int chunk_planes(int nx, int ny, int nz) {

@@ -161,15 +161,15 @@ constexpr unsigned kBlkKeep = 1u << 16;
 constexpr unsigned kBlkFirst = 1u << 17;
 constexpr unsigned kBlkFast = 1u << 18;
 constexpr int kBlkIncShift = 20;
-constexpr int kZDeep = 8;   // planes per block at most but for the last of a run (block_planes)
+constexpr int kZBlock = 4, kZDeep = 8;   // planes per block: usually, at most (block_planes)
 struct Tiles {
     int ntx, nty, nzc, zc;   // tiles along x and y, z chunks, planes per chunk
     int nz, zb;              // planes, planes per block (block_list chooses its own)
     int shortest() const { return zb < 3 ? 2 : zb - 1; }   // planes of a block, unless its run has fewer; s33's bands have two
     static int longest(int zb) { return 3 * zb - 4; }   // planes of a block at most (zb > 2): 2 shortest() + zb - 2
-    bool bands() const { return nty >= 8 && nz >= 8 * zb; }                 // see piece_xcd
+    bool bands() const { return nty >= 8 && nz >= 8 * kZBlock; }            // see piece_xcd
     bool boxes(int nx, int ny) const { return bands() && nty <= 24 && (long long)nx * ny * nz <= 1 << 20; }
-    int run() const { return (int)(((long long)ntx * nty * ((nz + zb - 1) / zb) + 511) / 512); }
+    int run() const { return (int)(((long long)ntx * nty * ((nz + kZBlock - 1) / kZBlock) + 511) / 512); }
     int ntiles;              // ntx * nty * nzc
     int cap;                 // entries per XCD at most
     int per;                 // entries per XCD: the grid has 8 * per blocks

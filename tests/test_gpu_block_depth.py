@@ -1,6 +1,7 @@
 """The stencil passes where the block list takes deep blocks (8 planes: many blocks, mostly solid) and
 its usual ones (4 planes: as many blocks, mostly fluid), on long grids whose ends leave remainders,
-against the FP64 oracle.
+and two planes with enough tile rows for eight bands, too few and just enough planes; against the
+FP64 oracle.
 
 Tolerances as the other parity tests: FP32 rounding of the fields gives about 1e-6 after a few
 steps, far below 1e-4; FP64 differs from the oracle by the order of its sums, below 1e-11.
@@ -25,7 +26,9 @@ def _gpu(request):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("shape,npml,fluid", [((33, 6, 13705), 1, 0.0), ((33, 6, 13699), 0, 0.0), ((33, 6, 13705), 1, 1.0)])
+@pytest.mark.parametrize("shape,npml,fluid", [
+    ((33, 6, 13705), 1, 0.0), ((33, 6, 13699), 0, 0.0), ((33, 6, 13705), 1, 1.0),
+    ((65, 33, 20), 2, 0.5), ((33, 40, 47), 3, 0.5)])
 @pytest.mark.parametrize("precision,tol", [("f32", 1e-4), ("f64", 1e-11)])
 def test_block_depths(shape, npml, fluid, precision, tol):
     sc = S.random_scenario(shape, seed=5, nsteps=6, npml=npml, nrec=300, fluid_fraction=fluid)
