@@ -337,7 +337,9 @@ typedef struct el_fluid_stats {
 /*
  *   enable: 1 use the fluid update where it applies (the default), 0 never,
  *           -1 keep the current setting.  A change waits for the plan's
- *           previous operation (host-blocking).
+ *           previous operation (host-blocking), but not for one that is being enqueued in
+ *           parts (a group's member, an executor's operation with a replay limit): that one
+ *           goes on under the setting it began with.
  *   *stats (host, may be NULL): the counts under the resulting setting (all
  *           zero when the fluid update is off).
  * Errors: EL_EINVAL for a NULL plan or an enable outside -1..1.

@@ -25,6 +25,7 @@ struct ExecSlot {
     hipEvent_t done = nullptr;
     hipEvent_t ready = nullptr;   // inputs written: recorded on the caller's stream
     el_plan plan = nullptr;
+    PassesOf began = {};          // the plan's passes when the operation was started
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     // what is left of the operation to enqueue (replay limit)
     int op = EL_OP_FORWARD;
@@ -65,28 +66,27 @@ el_status hipf(hipError_t e, const char *what) {
 // advances the counter; the adjoint velocity pass forms the increments Theta^T y of row *ctr - 1
 // in extra blocks and the adjoint stress pass adds them and steps the counter back.
 template <typename T>
-hipError_t launch_step(el_plan p, const Dev<T> &d, int op, void *traces, int *ctr, hipStream_t s) {
+hipError_t launch_step(const Passes<T> &ps, const Relax<T> &rx, int op, void *traces, int *ctr, hipStream_t s) {
     hipError_t e;
-    const Relax<T> &rx = plan_relax<T>(p);
     if (op == EL_OP_FORWARD) {
-        e = launch_velocity(d, p->tiles, s, &p->rec, static_cast<double *>(traces), nullptr, ctr);
-        if (e == hipSuccess) e = launch_relax(d, p->tiles, rx, false, s);
-        if (e == hipSuccess) e = launch_stress(d, p->tiles, s, ctr);
+        e = launch_velocity(ps.d, ps.tiles, s, &ps.rec, static_cast<double *>(traces), nullptr, ctr);
+        if (e == hipSuccess) e = launch_relax(ps.d, ps.tiles, rx, false, s);
+        if (e == hipSuccess) e = launch_stress(ps.d, ps.tiles, s, ctr);
     } else {
-        e = launch_adj_velocity(d, p->tiles, s, &p->rec, static_cast<const double *>(traces), ctr);
-        if (e == hipSuccess) e = launch_relax(d, p->tiles, rx, true, s);
-        if (e == hipSuccess) e = launch_adj_stress(d, p->tiles, s, ctr);
+        e = launch_adj_velocity(ps.d, ps.tiles, s, &ps.rec, static_cast<const double *>(traces), ctr);
+        if (e == hipSuccess) e = launch_relax(ps.d, ps.tiles, rx, true, s);
+        if (e == hipSuccess) e = launch_adj_stress(ps.d, ps.tiles, s, ctr);
     }
     return e;
 }
 
 template <typename T>
-el_status capture(el_plan p, const Dev<T> &d, int op, int steps, void *traces, int *ctr, hipStream_t s,
+el_status capture(const Passes<T> &ps, const Relax<T> &rx, int op, int steps, void *traces, int *ctr, hipStream_t s,
                   hipGraphExec_t *out) {
     hipGraph_t g = nullptr;
     EX_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
     hipError_t e = hipSuccess;
-    for (int m = 0; m < steps && e == hipSuccess; ++m) e = launch_step(p, d, op, traces, ctr, s);
+    for (int m = 0; m < steps && e == hipSuccess; ++m) e = launch_step(ps, rx, op, traces, ctr, s);
     const hipError_t e2 = hipStreamEndCapture(s, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
         if (e2 == hipSuccess && g) (void)hipGraphDestroy(g);
@@ -101,9 +101,10 @@ el_status capture(el_plan p, const Dev<T> &d, int op, int steps, void *traces, i
 // Enqueue the slot's remaining replays, at most ex->ahead of them in flight (all when
 // ahead = 0), then, once every replay is enqueued, the final work and completion events.
 template <typename T>
-el_status feed(el_exec ex, ExecSlot &sl, const Dev<T> &d) {
+el_status feed(el_exec ex, ExecSlot &sl) {
     if (sl.tail_done) return EL_OK;
     el_plan p = sl.plan;
+    const Passes<T> &ps = passes<T>(sl.began);
     const hipStream_t s = sl.stream;
     const int M = p->g.nsteps, L = p->nrec;
     const int cap = ex->ahead;
@@ -125,9 +126,9 @@ el_status feed(el_exec ex, ExecSlot &sl, const Dev<T> &d) {
     }
     if (sl.full_left > 0 || sl.rem_left) return EL_OK;
     if (sl.op == EL_OP_FORWARD)
-        EX_TRY(launch_gather(d, p->rec, static_cast<double *>(sl.out) + (size_t)(M - 1) * L, s), "gather");
-    if (p->fluid_path && p->fast_tiles > 0) EX_TRY(launch_fluid_fill(d, p->tiles, s), "fluid fill");
-    if (sl.op == EL_OP_ADJOINT) EX_TRY(launch_extract(d, static_cast<T *>(sl.out), s), "extract");
+        EX_TRY(launch_gather(ps.d, ps.rec, static_cast<double *>(sl.out) + (size_t)(M - 1) * L, s), "gather");
+    if (ps.fill) EX_TRY(launch_fluid_fill(ps.d, ps.tiles, s), "fluid fill");
+    if (sl.op == EL_OP_ADJOINT) EX_TRY(launch_extract(ps.d, static_cast<T *>(sl.out), s), "extract");
     EX_TRY(hipEventRecord(p->done, s), "record plan completion");
     EX_TRY(hipEventRecord(sl.done, s), "record slot completion");
     sl.tail_done = true;
@@ -136,13 +137,15 @@ el_status feed(el_exec ex, ExecSlot &sl, const Dev<T> &d) {
 
 el_status feed_slot(el_exec ex, ExecSlot &sl) {
     if (!sl.busy || sl.tail_done) return EL_OK;
-    return sl.plan->g.precision == EL_F64 ? feed(ex, sl, sl.plan->dd) : feed(ex, sl, sl.plan->df);
+    return sl.plan->g.precision == EL_F64 ? feed<double>(ex, sl) : feed<float>(ex, sl);
 }
 
 template <typename T>
-el_status start_op(el_exec ex, ExecSlot &sl, el_plan p, const Dev<T> &d, int op, const void *in, void *out,
-                   hipStream_t after) {
+el_status start_op(el_exec ex, ExecSlot &sl, el_plan p, int op, const void *in, void *out, hipStream_t after) {
     const hipStream_t s = sl.stream;
+    const Passes<T> &ps = passes<T>(sl.began) = plan_passes<T>(p);
+    const Dev<T> &d = ps.d;
+    const Relax<T> &rx = plan_relax<T>(p);
     const int M = p->g.nsteps, L = p->nrec;
     int *ctr = reinterpret_cast<int *>(p->ws + p->L.counter);
     void *traces = op == EL_OP_FORWARD ? out : const_cast<void *>(in);
@@ -151,12 +154,12 @@ el_status start_op(el_exec ex, ExecSlot &sl, el_plan p, const Dev<T> &d, int op,
     EX_TRY(hipStreamWaitEvent(s, sl.ready, 0), "order after the caller's stream");
     EX_TRY(hipStreamWaitEvent(s, p->done, 0), "order after the plan's previous operation");
     EX_TRY(launch_zero_state(d, s), "zero state");
-    EX_TRY(launch_relax_zero(p->tiles, plan_relax<T>(p), s), "relaxation state");
+    EX_TRY(launch_relax_zero(ps.tiles, rx, s), "relaxation state");
     if (op == EL_OP_FORWARD) {
         EX_TRY(launch_inject(d, static_cast<const T *>(in), s), "inject");
         EX_TRY(launch_set_counter(ctr, 0, s), "counter");
     } else {
-        EX_TRY(launch_scatter(d, p->rec, static_cast<const double *>(in) + (size_t)(M - 1) * L, s), "scatter");
+        EX_TRY(launch_scatter(d, ps.rec, static_cast<const double *>(in) + (size_t)(M - 1) * L, s), "scatter");
         EX_TRY(launch_set_counter(ctr, M - 1, s), "counter");
     }
     const int nupd = M - 1;
@@ -164,11 +167,11 @@ el_status start_op(el_exec ex, ExecSlot &sl, el_plan p, const Dev<T> &d, int op,
     const int nfull = K > 0 ? nupd / K : 0;
     const int rem = nupd - nfull * K;
     if (K > 0) {
-        el_status st = capture(p, d, op, K, traces, ctr, s, &sl.graph[0]);
+        el_status st = capture(ps, rx, op, K, traces, ctr, s, &sl.graph[0]);
         if (st != EL_OK) return st;
     }
     if (rem > 0) {
-        el_status st = capture(p, d, op, rem, traces, ctr, s, &sl.graph[1]);
+        el_status st = capture(ps, rx, op, rem, traces, ctr, s, &sl.graph[1]);
         if (st != EL_OK) return st;
     }
     sl.op = op;
@@ -178,7 +181,7 @@ el_status start_op(el_exec ex, ExecSlot &sl, el_plan p, const Dev<T> &d, int op,
     sl.rem_left = rem > 0;
     sl.tail_done = false;
     sl.head = sl.count = 0;
-    return feed<T>(ex, sl, d);
+    return feed<T>(ex, sl);
 }
 
 void release(ExecSlot &sl) {
@@ -279,8 +282,8 @@ el_status el_exec_start(el_exec ex, el_plan plan, int32_t op, const void *in, vo
     ExecSlot &sl = ex->slots[k];
     sl.plan = plan;
     const hipStream_t after = reinterpret_cast<hipStream_t>(stream);
-    st = plan->g.precision == EL_F64 ? start_op(ex, sl, plan, plan->dd, op, in, out, after)
-                                     : start_op(ex, sl, plan, plan->df, op, in, out, after);
+    st = plan->g.precision == EL_F64 ? start_op<double>(ex, sl, plan, op, in, out, after)
+                                     : start_op<float>(ex, sl, plan, op, in, out, after);
     if (st != EL_OK) {
         (void)hipStreamSynchronize(sl.stream);
         release(sl);

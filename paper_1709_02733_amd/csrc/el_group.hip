@@ -23,6 +23,7 @@ struct Member {
     bool running = false;   // takes part in the coming ticks
     bool withdrawn = false;
     el_plan plan = nullptr;
+    PassesOf began = {};    // the plan's passes when the member joined
     int op = EL_OP_FORWARD;
     const void *in = nullptr;
     void *out = nullptr;
@@ -54,10 +55,6 @@ el_status hipf(hipError_t e, const char *what) {
         if (e_ != hipSuccess) return hipf(e_, what); \
     } while (0)
 
-template <typename T> Dev<T> &plan_dev(el_plan p);
-template <> Dev<float> &plan_dev<float>(el_plan p) { return p->df; }
-template <> Dev<double> &plan_dev<double>(el_plan p) { return p->dd; }
-
 el_status check_group(el_group g) {
     if (!g) return el::set_error(EL_EINVAL, "group is NULL");
     int dev = -1;
@@ -77,13 +74,13 @@ el_status check_slot(el_group g, int slot) {
 template <typename T>
 el_status finish(el_group g, Member &mb) {
     el_plan p = mb.plan;
-    const Dev<T> &d = plan_dev<T>(p);
+    const Passes<T> &ps = passes<T>(mb.began);
     const hipStream_t s = g->stream;
     if (!mb.withdrawn) {
         if (mb.op == EL_OP_FORWARD && p->nrec > 0)
-            GR_TRY(launch_gather(d, p->rec, static_cast<double *>(mb.out) + (size_t)mb.total * p->nrec, s), "gather");
-        if (p->fluid_path && p->fast_tiles > 0) GR_TRY(launch_fluid_fill(d, p->tiles, s), "fluid fill");
-        if (mb.op == EL_OP_ADJOINT) GR_TRY(launch_extract(d, static_cast<T *>(mb.out), s), "extract");
+            GR_TRY(launch_gather(ps.d, ps.rec, static_cast<double *>(mb.out) + (size_t)mb.total * p->nrec, s), "gather");
+        if (ps.fill) GR_TRY(launch_fluid_fill(ps.d, ps.tiles, s), "fluid fill");
+        if (mb.op == EL_OP_ADJOINT) GR_TRY(launch_extract(ps.d, static_cast<T *>(mb.out), s), "extract");
     }
     GR_TRY(hipEventRecord(p->done, s), "record plan completion");
     GR_TRY(hipEventRecord(mb.done, s), "record member completion");
@@ -94,15 +91,16 @@ el_status finish(el_group g, Member &mb) {
 template <typename T>
 el_status start(el_group g, Member &mb) {
     el_plan p = mb.plan;
-    const Dev<T> &d = plan_dev<T>(p);
+    const Passes<T> &ps = passes<T>(mb.began) = plan_passes<T>(p);
+    const Dev<T> &d = ps.d;
     const hipStream_t s = g->stream;
     const int M = p->g.nsteps, L = p->nrec;
     GR_TRY(launch_zero_state(d, s), "zero state");
-    GR_TRY(launch_relax_zero(p->tiles, plan_relax<T>(p), s), "relaxation state");
+    GR_TRY(launch_relax_zero(ps.tiles, plan_relax<T>(p), s), "relaxation state");
     if (mb.op == EL_OP_FORWARD)
         GR_TRY(launch_inject(d, static_cast<const T *>(mb.in), s), "inject");
     else
-        GR_TRY(launch_scatter(d, p->rec, static_cast<const double *>(mb.in) + (size_t)(M - 1) * L, s), "scatter");
+        GR_TRY(launch_scatter(d, ps.rec, static_cast<const double *>(mb.in) + (size_t)(M - 1) * L, s), "scatter");
     mb.running = true;
     if (mb.total == 0) return finish<T>(g, mb);
     return EL_OK;
@@ -122,26 +120,26 @@ el_status grouped(el_group g, const Batch &b, int pass) {
     int blocks = 0;
     for (int q = 0; q < b.n; ++q) {
         Member &mb = *b.mb[q];
-        el_plan p = mb.plan;
-        const int L = p->nrec, M = p->g.nsteps;
-        gp.d[q] = plan_dev<T>(p);
-        gp.tl[q] = p->tiles;
+        const Passes<T> &ps = passes<T>(mb.began);
+        const int L = mb.plan->nrec, M = mb.plan->g.nsteps;
+        gp.d[q] = ps.d;
+        gp.tl[q] = ps.tiles;
         gp.r[q] = Rec{};
         gp.row[q] = nullptr;
         gp.first[q] = blocks;
-        blocks += 8 * p->tiles.per;
+        blocks += 8 * ps.tiles.per;
         if (pass == 0 && L > 0) {
             // forward update k is m = k+1; its velocity pass gathers row m-1 = k
-            gp.r[q] = p->rec;
+            gp.r[q] = ps.rec;
             gp.row[q] = static_cast<double *>(mb.out) + (size_t)mb.steps * L;
             blocks += gather_blocks(L);
         }
-        if (pass == 2 && p->rec.npts > 0) {
+        if (pass == 2 && ps.rec.npts > 0) {
             // adjoint update k is m = M-1-k; its velocity pass forms the increments Theta^T y of
             // row m-1, which its stress pass adds
-            gp.r[q] = p->rec;
+            gp.r[q] = ps.rec;
             gp.row[q] = const_cast<double *>(static_cast<const double *>(mb.in)) + (size_t)(M - 2 - mb.steps) * L;
-            blocks += scatter_blocks(p->rec.npts);
+            blocks += scatter_blocks(ps.rec.npts);
         }
         blocks = (blocks + 7) / 8 * 8;
     }
@@ -169,8 +167,8 @@ el_status tick(el_group g) {
     for (auto &mb : g->m)
         if (mb.running) {
             const Relax<T> &rx = plan_relax<T>(mb.plan);
-            GR_TRY(launch_relax(plan_dev<T>(mb.plan), mb.plan->tiles, rx, mb.op == EL_OP_ADJOINT, g->stream),
-                   "relaxation");
+            const Passes<T> &ps = passes<T>(mb.began);
+            GR_TRY(launch_relax(ps.d, ps.tiles, rx, mb.op == EL_OP_ADJOINT, g->stream), "relaxation");
         }
     for (auto &b : fwd)
         if ((st = grouped<T>(g, b, 1)) != EL_OK) return st;

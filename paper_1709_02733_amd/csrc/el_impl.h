@@ -448,3 +448,29 @@ struct el_plan_ {
 template <typename T> inline el::Relax<T> &plan_relax(el_plan_ *p);
 template <> inline el::Relax<float> &plan_relax<float>(el_plan_ *p) { return p->rf; }
 template <> inline el::Relax<double> &plan_relax<double>(el_plan_ *p) { return p->rd; }
+
+// What a plan's passes take under its present fluid-update setting.  An operation that is enqueued
+// in parts (el_exec, el_group) keeps the copy it began with: el_plan_fluid_path may change the
+// setting in between, and the rest of the operation must still read the stresses (and only those)
+// that its earlier passes stored.
+template <typename T>
+struct Passes {
+    el::Dev<T> d;
+    el::Tiles tiles;
+    el::Rec rec;
+    bool fill;               // some tiles are fluid: k_fluid_fill ends the operation
+};
+template <typename T> inline el::Dev<T> &plan_dev(el_plan_ *p);
+template <> inline el::Dev<float> &plan_dev<float>(el_plan_ *p) { return p->df; }
+template <> inline el::Dev<double> &plan_dev<double>(el_plan_ *p) { return p->dd; }
+template <typename T> inline Passes<T> plan_passes(el_plan_ *p) {
+    return Passes<T>{plan_dev<T>(p), p->tiles, p->rec, p->fluid_path && p->fast_tiles > 0};
+}
+// Both precisions' places for such a copy; one is used.
+struct PassesOf {
+    Passes<float> f;
+    Passes<double> d;
+};
+template <typename T> inline Passes<T> &passes(PassesOf &o);
+template <> inline Passes<float> &passes<float>(PassesOf &o) { return o.f; }
+template <> inline Passes<double> &passes<double>(PassesOf &o) { return o.d; }
