@@ -96,6 +96,7 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
         const Tiles t = make_tiles(g.nx, g.ny, g.nz);
         // increments: the planes of a sub-tile's piece with points, at most every plane there is
         const size_t planes = std::min(E * Tiles::longest(kZDeep), (size_t)4 * t.ntx * t.nty * g.nz);
+        L->inc_planes = (long long)planes;
         for (size_t &o : L->csr_pos) o = take(E * 4);
         for (size_t &o : L->inc) o = take(planes * kWaveX * kWaveY * es);
         for (size_t &o : L->tile_order) o = take((size_t)8 * t.cap * sizeof(BlockEnt<double>));
@@ -126,6 +127,7 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
 constexpr int kZChunk = 6;
 constexpr long long kMinTiles = 4096;
 constexpr int kMaxTiles = (1 << 24) - 1;   // (arrays below 4 GiB keep under it)
+constexpr long long kFewBlocks = 5120, kManyBlocks = 10240;   // see block_planes
 int chunk_planes(int nx, int ny, int nz) {
     const long long cols = (long long)((nx + kTileX - 1) / kTileX) * ((ny + kTileY - 1) / kTileY);
     int zc = kZChunk;
@@ -144,13 +146,15 @@ Tiles make_tiles(int nx, int ny, int nz) {
     t.order = nullptr;
     t.per = t.cap = 0;
     // an XCD's entries at most: four per piece.  The pieces of a tile column are at least two planes
-    // apart but for a last one; with chunks of kZChunk planes (and so blocks of kZBlock at least) a
-    // run of D planes has at most (D + 1) / 3, seven in 18 planes
+    // apart but for a last one; with blocks of kZBlock at least and runs of kZChunk planes (every
+    // plane of a tile column is in an entry, so block_planes counts cols nz planes or more) a run of
+    // D planes has at most (D + 1) / 3, seven in 18 planes
+    const bool deep = t.zc == kZChunk && (long long)t.ntx * t.nty * nz >= kFewBlocks * kZBlock;
     long long cnt[8] = {}, all = 0;
     for (int by = 0; by < t.nty; ++by)
         for (int z0 = 0, z1 = 0; z0 < nz; z0 = z1) {
             for (z1 = z0 + 1; z1 < nz && z1 * 8 / nz == z0 * 8 / nz; ++z1) {}
-            const int n = 4 * t.ntx * (t.zc == kZChunk ? 7 * (z1 - z0) / 18 + 2 : (z1 - z0 + 1) / 2 + 1);
+            const int n = 4 * t.ntx * (deep ? 7 * (z1 - z0) / 18 + 2 : (z1 - z0 + 1) / 2 + 1);
             cnt[piece_xcd(t, by, z0, 0)] += n;
             all += n;
         }
@@ -243,7 +247,6 @@ Subs subs_of(const Tiles &t, int nx, int ny, const unsigned char *fast, const un
 // 67.6/73.6, 76.4/80.3; 203 x 187 x 150 (14288) 223/251, 222/251, 220/250, 225/254; 256^3 564/611,
 // 554/601, 558/601, 561/605; 384^3 1760/1886, 1731/1846, 1721/1829, 1719/1823; 192^3 in double
 // precision (13824) 545/612, 534/599, 532/596, 540/598.
-constexpr long long kFewBlocks = 5120, kManyBlocks = 10240;
 int block_planes(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes) {
     long long planes = 0;        // over the entries
     long long subs = 0, general = 0;   // sub-tiles
@@ -436,7 +439,8 @@ BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsi
                 const Subs u = subs_of(t, nx, ny, fast, lanes, bx, by, q);
                 auto put = [&](unsigned flags) {
                     e.flags = flags | (count[x] == first ? kBlkFirst : 0u);
-                    order[8 * count[x]++ + x] = e;
+                    if (count[x] < (size_t)t.cap) order[8 * count[x] + x] = e;
+                    ++count[x];
                 };
                 if (fast && fast[q]) {
                     unsigned edges = tile_edges(t, fast, q) & 3u;
@@ -458,6 +462,9 @@ BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsi
                 piece.push_back({8 * first + x, (int)(count[x] - first), z, cut, 0u, 0});
                 begins[(size_t)z * step + by * t.ntx + bx] = (int)piece.size();
             }
+    const size_t per = *std::max_element(count, count + 8);
+    out.fits = per <= (size_t)t.cap;
+    if (!out.fits) return out;
     // increments: the planes of every sub-tile's piece with points, one after the other; a point's
     // element there (plane, then lane)
     const size_t np = points.size() / 3;
@@ -486,13 +493,15 @@ BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsi
         const int plane = p.slot + __builtin_popcount(p.with & ((1u << sub) - 1u)) * (p.z1 - p.z0) + k - p.z0;
         out.pos[q] = (plane * kWaveY + j % kWaveY) * kWaveX + i % kWaveX;
     }
-    size_t per = 0;
-    for (int x = 0; x < 8; ++x) per = std::max(per, count[x]);
     out.per = (int)per;
     for (int x = 0; x < 8; ++x)
         for (size_t e = count[x]; e < per; ++e) order[8 * e + x] = BlockEnt<T>{};
     return out;
 }
+template BlockList<float> block_list<float>(const Tiles &, int, int, int, const unsigned char *, const unsigned char *,
+                                            const unsigned long long *, const float *, const std::vector<int> &);
+template BlockList<double> block_list<double>(const Tiles &, int, int, int, const unsigned char *, const unsigned char *,
+                                              const unsigned long long *, const double *, const std::vector<int> &);
 
 }  // namespace el
 
@@ -789,6 +798,9 @@ el_status set_tables_t(el_plan p, Dev<T> &d, hipStream_t s) {
     if (p->per[on] == 0 && p->tiles.ntiles > 0) {
         const BlockList<T> list = block_list<T>(p->tiles, p->g.nx, p->g.ny, p->g.npml, fast, p->uni.data(), p->lanes.data(),
                                                 reinterpret_cast<const T *>(p->med.data()), p->points);
+        if (!list.fits) return fail(EL_EINVAL, "the block list needs more than %d entries per XCD", p->tiles.cap);
+        if (list.planes > p->L.inc_planes)
+            return fail(EL_EINVAL, "the receivers need %lld planes of increments, room for %lld", list.planes, p->L.inc_planes);
         HIP_TRY(hipMemcpyAsync(ws + p->L.tile_order[on], list.entries.get(), 8 * (size_t)list.per * sizeof(BlockEnt<T>),
                                hipMemcpyHostToDevice, s), "block list");
         HIP_TRY(launch_zero_inc(d, list.planes * kWaveX * kWaveY, s), "increments");

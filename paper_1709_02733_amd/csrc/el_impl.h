@@ -186,6 +186,7 @@ int piece_xcd(const Tiles &t, int by, int z, long long index);
 template <typename T>
 struct BlockList {
     std::unique_ptr<BlockEnt<T>[]> entries;
+    bool fits = true;        // false: an XCD's entries outgrow their room, and there is no list
     int per = 0;
     long long planes = 0;    // increment planes of kWaveX x kWaveY elements
     std::vector<int> pos;    // each point's element in them
@@ -317,6 +318,7 @@ struct Layout {
                              // (a, b) over both arrays of a position)
     size_t rec_idx, rec_w, csr_pt, csr_ptc, csr_row, csr_rec, csr_w;
     size_t rec_fl[2], csr_pos[2], inc[2];   // without, with the fluid update (as tile_order)
+    long long inc_planes;    // room of each inc, in planes of kWaveX x kWaveY elements
     size_t stats;            // media statistics (16 doubles)
     size_t counter;          // device step counter of captured step graphs
     size_t tile_order[2];    // block lists of the stencil passes (8 * cap entries)
