@@ -784,42 +784,46 @@ el_status upload_receivers(el_plan_ *p, const double *rec, hipStream_t s) {
 }
 
 // The block list, the receiver corners' fluid flags and the points' places in the increments, with
-// the fluid tiles when the fluid update is enabled and without them otherwise.  Each setting has
+// the fluid tiles when the fluid update is on and without them otherwise.  Each setting has
 // tables of its own, made when it is first asked for, so a launch captured under one stays whole.
+// The plan takes them once they are complete: a failure leaves it as it was.
 template <typename T>
-el_status set_tables_t(el_plan p, Dev<T> &d, hipStream_t s) {
-    const int on = p->fluid_path ? 1 : 0;
+el_status set_tables_t(el_plan p, Dev<T> &d, bool fluid, hipStream_t s) {
+    const int on = fluid ? 1 : 0;
     const unsigned char *fast = on ? p->fast.data() : nullptr;
     char *ws = p->ws;
-    d.incoff = (unsigned)(p->L.inc[on] >> 8);
-    p->rec.fl = reinterpret_cast<unsigned char *>(ws + p->L.rec_fl[on]);
-    p->rec.pos = reinterpret_cast<int *>(ws + p->L.csr_pos[on]);
-    p->tiles.order = ws + p->L.tile_order[on];
+    Dev<T> nd = d;
+    nd.incoff = (unsigned)(p->L.inc[on] >> 8);
     if (p->per[on] == 0 && p->tiles.ntiles > 0) {
         const BlockList<T> list = block_list<T>(p->tiles, p->g.nx, p->g.ny, p->g.npml, fast, p->uni.data(), p->lanes.data(),
                                                 reinterpret_cast<const T *>(p->med.data()), p->points);
         if (!list.fits) return fail(EL_EINVAL, "the block list needs more than %d entries per XCD", p->tiles.cap);
         if (list.planes > p->L.inc_planes)
             return fail(EL_EINVAL, "the receivers need %lld planes of increments, room for %lld", list.planes, p->L.inc_planes);
-        HIP_TRY(hipMemcpyAsync(ws + p->L.tile_order[on], list.entries.get(), 8 * (size_t)list.per * sizeof(BlockEnt<T>),
-                               hipMemcpyHostToDevice, s), "block list");
-        HIP_TRY(launch_zero_inc(d, list.planes * kWaveX * kWaveY, s), "increments");
         std::vector<unsigned char> fl(p->rec_tile.size(), 0);
         for (size_t e = 0; e < fl.size(); ++e) fl[e] = fast && fast[p->rec_tile[e]] ? 1 : 0;
+        HIP_TRY(hipMemcpyAsync(ws + p->L.tile_order[on], list.entries.get(), 8 * (size_t)list.per * sizeof(BlockEnt<T>),
+                               hipMemcpyHostToDevice, s), "block list");
+        HIP_TRY(launch_zero_inc(nd, list.planes * kWaveX * kWaveY, s), "increments");
         if (!fl.empty()) {
-            HIP_TRY(hipMemcpyAsync((void *)p->rec.fl, fl.data(), fl.size(), hipMemcpyHostToDevice, s), "receiver flags");
-            HIP_TRY(hipMemcpyAsync((void *)p->rec.pos, list.pos.data(), list.pos.size() * 4, hipMemcpyHostToDevice, s),
+            HIP_TRY(hipMemcpyAsync(ws + p->L.rec_fl[on], fl.data(), fl.size(), hipMemcpyHostToDevice, s), "receiver flags");
+            HIP_TRY(hipMemcpyAsync(ws + p->L.csr_pos[on], list.pos.data(), list.pos.size() * 4, hipMemcpyHostToDevice, s),
                     "increments");
         }
         HIP_TRY(hipStreamSynchronize(s), "block list");
         p->per[on] = list.per;
     }
+    d = nd;
+    p->rec.fl = reinterpret_cast<unsigned char *>(ws + p->L.rec_fl[on]);
+    p->rec.pos = reinterpret_cast<int *>(ws + p->L.csr_pos[on]);
+    p->tiles.order = ws + p->L.tile_order[on];
     p->tiles.per = p->per[on];
+    p->fluid_path = fluid;
     return EL_OK;
 }
 
-el_status set_tables(el_plan p, hipStream_t s) {
-    return p->g.precision == EL_F64 ? set_tables_t(p, p->dd, s) : set_tables_t(p, p->df, s);
+el_status set_tables(el_plan p, bool fluid, hipStream_t s) {
+    return p->g.precision == EL_F64 ? set_tables_t(p, p->dd, fluid, s) : set_tables_t(p, p->df, fluid, s);
 }
 
 el_status check_plan(el_plan p) {
@@ -1107,7 +1111,7 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
                 p->fast_skipped += (long long)std::max(0, w[a] - 2 * lo - 2 * hi) * w[(a + 1) % 3] * w[(a + 2) % 3];
             }
         }
-        st = set_tables(p, s);
+        st = set_tables(p, true, s);
         if (st != EL_OK) return bail(st);
     }
     e = hipStreamSynchronize(s);
@@ -1260,8 +1264,7 @@ el_status el_plan_fluid_path(el_plan p, int32_t enable, el_fluid_stats *stats) {
     if (enable != -1 && enable != 0 && enable != 1) return fail(EL_EINVAL, "enable must be -1, 0 or 1");
     if (enable >= 0 && (enable != 0) != p->fluid_path) {
         HIP_TRY(hipEventSynchronize(p->done), "wait for the plan's previous operation");
-        p->fluid_path = enable != 0;
-        st = set_tables(p, nullptr);
+        st = set_tables(p, enable != 0, nullptr);
         if (st != EL_OK) return st;
     }
     if (stats) {
