@@ -57,7 +57,7 @@ typedef int32_t el_status;
 #define EL_EINVAL    -1   /* malformed argument, bad material value, null pointer          */
 #define EL_EUNSTABLE -2   /* CFL above 6/(7 sqrt 3) or dt*alpha outside [0,1)               */
 #define EL_ERANGE    -3   /* a receiver outside [0, n-1]*dx on some axis                    */
-#define EL_ENOMEM    -4   /* workspace smaller than el_plan_bytes() says                    */
+#define EL_ENOMEM    -4   /* workspace smaller than el_plan_bytes() says; host memory ran out */
 #define EL_EDEVICE   -5   /* a HIP runtime call failed                                      */
 #define EL_EBUSY     -6   /* every executor or group slot is in use                         */
 

@@ -5,7 +5,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <string>
 #include <vector>
 
 #include "el_impl.h"
@@ -14,7 +13,7 @@ using namespace el;
 
 namespace {
 
-thread_local std::string g_err;
+thread_local char g_err[512];
 
 #define fail el::set_error
 
@@ -41,12 +40,10 @@ const double kRecSlack = 1e-9;
 namespace el {
 
 el_status set_error(el_status st, const char *fmt, ...) {
-    char buf[512];
     va_list ap;
     va_start(ap, fmt);
-    vsnprintf(buf, sizeof buf, fmt, ap);
+    vsnprintf(g_err, sizeof g_err, fmt, ap);
     va_end(ap);
-    g_err = buf;
     return st;
 }
 
@@ -522,7 +519,7 @@ const char *el_status_string(el_status s) {
     }
 }
 
-const char *el_last_error(void) { return g_err.c_str(); }
+const char *el_last_error(void) { return g_err; }
 
 el_status el_grid_check(const el_grid *g, const double *rec, int32_t nrec) {
     if (!g) return fail(EL_EINVAL, "grid is NULL");
@@ -840,12 +837,14 @@ hipError_t timed(el_plan p, int kind, int m, hipStream_t s, F launch) {
     if (p->timing_every <= 0 || m % p->timing_every != 0) return launch();
     auto &v = p->ev[kind];
     if (p->used[kind] == v.size()) {
-        hipEvent_t a, b;
-        hipError_t e = hipEventCreate(&a);
-        if (e != hipSuccess) return e;
-        e = hipEventCreate(&b);
-        if (e != hipSuccess) return e;
-        v.emplace_back(a, b);
+        v.emplace_back(nullptr, nullptr);
+        hipError_t e = hipEventCreate(&v.back().first);
+        if (e == hipSuccess) e = hipEventCreate(&v.back().second);
+        if (e != hipSuccess) {
+            if (v.back().first) (void)hipEventDestroy(v.back().first);
+            v.pop_back();
+            return e;
+        }
     }
     auto &pr = v[p->used[kind]++];
     hipError_t e = hipEventRecord(pr.first, s);
@@ -921,7 +920,7 @@ extern "C" {
 
 el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, const float *mu, const float *rho,
                          const float *alpha, const float *alpha_r, const double *rec, int32_t nrec, void *workspace,
-                         size_t workspace_bytes, void *stream) {
+                         size_t workspace_bytes, void *stream) try {
     if (!out) return fail(EL_EINVAL, "out is NULL");
     *out = nullptr;
     el_status st = el_grid_check(grid, rec, nrec);
@@ -938,7 +937,8 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
 
-    el_plan_ *p = new el_plan_();
+    std::unique_ptr<el_plan_, el_status (*)(el_plan)> own(new el_plan_(), el_plan_destroy);   // until it is whole
+    el_plan_ *p = own.get();
     p->g = *grid;
     p->nrec = nrec;
     p->N = (long long)grid->nx * grid->ny * grid->nz;
@@ -946,33 +946,27 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
     p->ws = static_cast<char *>(workspace);
     p->device = dev;
     p->tiles = make_tiles(grid->nx, grid->ny, grid->nz);
-    auto bail = [&](el_status e) {
-        if (p->done) (void)hipEventDestroy(p->done);
-        delete p;
-        return e;
-    };
-
     // media checks on the device, in double
     double *stats = reinterpret_cast<double *>(p->ws + L.stats);
     double *partial = reinterpret_cast<double *>(p->ws + L.partial);
     hipError_t e = launch_media_stats(lam, mu, rho, alpha, p->N, grid->dt, stats, partial, s);
-    if (e != hipSuccess) return bail(hip_fail(e, "media statistics"));
+    if (e != hipSuccess) return hip_fail(e, "media statistics");
     double hs[kStats];
     e = hipMemcpyAsync(hs, stats, sizeof hs, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return bail(hip_fail(e, "media statistics"));
-    if (hs[6] > 0) return bail(fail(EL_EINVAL, "%.0f non-finite material values", hs[6]));
-    if (!(hs[1] > 0)) return bail(fail(EL_EINVAL, "rho must be > 0 (min %.6g)", hs[1]));
-    if (hs[2] < 0) return bail(fail(EL_EINVAL, "mu must be >= 0 (min %.6g)", hs[2]));
-    if (!(hs[3] > 0)) return bail(fail(EL_EINVAL, "lambda + 2 mu must be > 0 (min %.6g)", hs[3]));
+    if (e != hipSuccess) return hip_fail(e, "media statistics");
+    if (hs[6] > 0) return fail(EL_EINVAL, "%.0f non-finite material values", hs[6]);
+    if (!(hs[1] > 0)) return fail(EL_EINVAL, "rho must be > 0 (min %.6g)", hs[1]);
+    if (hs[2] < 0) return fail(EL_EINVAL, "mu must be >= 0 (min %.6g)", hs[2]);
+    if (!(hs[3] > 0)) return fail(EL_EINVAL, "lambda + 2 mu must be > 0 (min %.6g)", hs[3]);
     // a positive bulk modulus (Sec. 2.1): the adjoint state w = C s divides by 3 lambda + 2 mu
-    if (!(hs[7] > 0)) return bail(fail(EL_EINVAL, "3 lambda + 2 mu must be > 0 (min %.6g)", hs[7]));
+    if (!(hs[7] > 0)) return fail(EL_EINVAL, "3 lambda + 2 mu must be > 0 (min %.6g)", hs[7]);
     if (hs[5] < 0 || hs[4] >= 1.0)
-        return bail(fail(EL_EUNSTABLE, "dt*alpha must lie in [0, 1) (range %.6g .. %.6g)", hs[5], hs[4]));
+        return fail(EL_EUNSTABLE, "dt*alpha must lie in [0, 1) (range %.6g .. %.6g)", hs[5], hs[4]);
     p->cmax = std::sqrt(hs[0]);
     const double cfl = p->cmax * grid->dt / grid->dx;
     if (cfl > kCflMax)
-        return bail(fail(EL_EUNSTABLE, "CFL c_max dt/dx = %.6g exceeds the 4th-order staggered limit %.6g", cfl, kCflMax));
+        return fail(EL_EUNSTABLE, "CFL c_max dt/dx = %.6g exceeds the 4th-order staggered limit %.6g", cfl, kCflMax);
     if (grid->relax.nmech > 0) {
         // alpha_r: finite, >= 0, and zero within npml + 2 cells of a face
         const int margin = grid->npml > 0 ? grid->npml + 2 : 0;
@@ -980,32 +974,31 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
         double rs[3] = {0, 0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(rs, stats + 8, sizeof rs, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return bail(hip_fail(e, "relaxation strength statistics"));
-        if (rs[1] > 0) return bail(fail(EL_EINVAL, "%.0f non-finite alpha_r values", rs[1]));
-        if (rs[0] < 0) return bail(fail(EL_EINVAL, "alpha_r must be >= 0 (min %.6g)", rs[0]));
+        if (e != hipSuccess) return hip_fail(e, "relaxation strength statistics");
+        if (rs[1] > 0) return fail(EL_EINVAL, "%.0f non-finite alpha_r values", rs[1]);
+        if (rs[0] < 0) return fail(EL_EINVAL, "alpha_r must be >= 0 (min %.6g)", rs[0]);
         if (rs[2] > 0)
-            return bail(fail(EL_EINVAL, "alpha_r must be 0 within npml + 2 = %d cells of a face (max there %.6g)",
-                             margin, rs[2]));
+            return fail(EL_EINVAL, "alpha_r must be 0 within npml + 2 = %d cells of a face (max there %.6g)", margin, rs[2]);
     }
 
     e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming);
-    if (e != hipSuccess) return bail(hip_fail(e, "event"));
+    if (e != hipSuccess) return hip_fail(e, "event");
     if (grid->precision == EL_F64) {
         bind(p->dd, p);
         bind_relax(p->rd, p);
         e = launch_convert_maps(p->dd, lam, mu, rho, alpha, s);
         if (e == hipSuccess && p->rd.L > 0) e = launch_relax_setup(p->dd, p->tiles, alpha_r, p->rd, s);
-        if (e != hipSuccess) return bail(hip_fail(e, "copy maps"));
+        if (e != hipSuccess) return hip_fail(e, "copy maps");
         st = upload_pml(p, p->dd, s);
     } else {
         bind(p->df, p);
         bind_relax(p->rf, p);
         e = launch_convert_maps(p->df, lam, mu, rho, alpha, s);
         if (e == hipSuccess && p->rf.L > 0) e = launch_relax_setup(p->df, p->tiles, alpha_r, p->rf, s);
-        if (e != hipSuccess) return bail(hip_fail(e, "copy maps"));
+        if (e != hipSuccess) return hip_fail(e, "copy maps");
         st = upload_pml(p, p->df, s);
     }
-    if (st != EL_OK) return bail(st);
+    if (st != EL_OK) return st;
     if (grid->relax.nmech > 0 && p->tiles.ntiles > 0) {
         std::vector<unsigned char> rflag(p->tiles.ntiles, 0);
         std::vector<int> rcount(p->tiles.ntiles, 0);
@@ -1013,7 +1006,7 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
         if (e == hipSuccess)
             e = hipMemcpyAsync(rcount.data(), p->ws + L.relax_count, rcount.size() * sizeof(int), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return bail(hip_fail(e, "relaxation tiles"));
+        if (e != hipSuccess) return hip_fail(e, "relaxation tiles");
         const Tiles &t = p->tiles;
         // the point list: the points of tile q start at roff[q] (tiles in index order)
         std::vector<long long> roff(t.ntiles, 0);
@@ -1031,16 +1024,16 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
         // a point keeps its element index in 30 bits
         const long long elements = (long long)(grid->precision == EL_F64 ? p->dd.plane() : p->df.plane()) * (grid->nz + 4);
         if (elements > (long long)kRelaxElemMask + 1)
-            return bail(fail(EL_EINVAL, "relaxation needs a padded grid of at most 2^30 elements (%lld)", elements));
+            return fail(EL_EINVAL, "relaxation needs a padded grid of at most 2^30 elements (%lld)", elements);
         e = hipMemcpyAsync(p->ws + L.relax_off, roff.data(), roff.size() * sizeof(long long), hipMemcpyHostToDevice, s);
         p->rf.npts = p->rd.npts = npts;
         if (e == hipSuccess)
             e = grid->precision == EL_F64 ? launch_relax_compact(p->dd, t, p->rd, s) : launch_relax_compact(p->df, t, p->rf, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return bail(hip_fail(e, "relaxation point list"));
+        if (e != hipSuccess) return hip_fail(e, "relaxation point list");
     }
     st = upload_receivers(p, rec, s);
-    if (st != EL_OK) return bail(st);
+    if (st != EL_OK) return st;
     {
         // fluid tiles (el_kernels.hip, k_classify), then the order table
         unsigned char *flags = reinterpret_cast<unsigned char *>(p->ws + L.tile_flags);
@@ -1063,7 +1056,7 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
         if (e == hipSuccess && p->tiles.ntiles > 0)
             e = hipMemcpyAsync(p->uni.data(), uflags, p->uni.size(), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return bail(hip_fail(e, "fluid tiles"));
+        if (e != hipSuccess) return hip_fail(e, "fluid tiles");
         const Tiles &t = p->tiles;
         const int P = grid->npml;
         const int n[3] = {grid->nx, grid->ny, grid->nz};
@@ -1112,15 +1105,15 @@ el_status el_plan_create(el_plan *out, const el_grid *grid, const float *lam, co
             }
         }
         st = set_tables(p, true, s);
-        if (st != EL_OK) return bail(st);
+        if (st != EL_OK) return st;
     }
     e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return bail(hip_fail(e, "plan set-up"));
+    if (e != hipSuccess) return hip_fail(e, "plan set-up");
     e = hipEventRecord(p->done, s);
-    if (e != hipSuccess) return bail(hip_fail(e, "event"));
-    *out = p;
+    if (e != hipSuccess) return hip_fail(e, "event");
+    *out = own.release();
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_plan_destroy(el_plan p) {
     if (!p) return EL_OK;
@@ -1159,7 +1152,7 @@ el_status el_plan_kernel_time(el_plan p, int32_t kind, int64_t *launches, double
     return EL_OK;
 }
 
-el_status el_forward(el_plan p, const void *p0, double *traces, void *stream) {
+el_status el_forward(el_plan p, const void *p0, double *traces, void *stream) try {
     el_status st = check_plan(p);
     if (st != EL_OK) return st;
     if (!p0 || (!traces && p->nrec > 0)) return fail(EL_EINVAL, "p0 or traces is NULL");
@@ -1170,9 +1163,9 @@ el_status el_forward(el_plan p, const void *p0, double *traces, void *stream) {
     if (st != EL_OK) return st;
     HIP_TRY(hipEventRecord(p->done, s), "record completion");
     return EL_OK;
-}
+} EL_CATCH
 
-el_status el_forward_energy(el_plan p, const void *p0, double *traces, int32_t every, double *energy, void *stream) {
+el_status el_forward_energy(el_plan p, const void *p0, double *traces, int32_t every, double *energy, void *stream) try {
     el_status st = check_plan(p);
     if (st != EL_OK) return st;
     if (!p0 || (!traces && p->nrec > 0)) return fail(EL_EINVAL, "p0 or traces is NULL");
@@ -1189,9 +1182,9 @@ el_status el_forward_energy(el_plan p, const void *p0, double *traces, int32_t e
     if (st != EL_OK) return st;
     HIP_TRY(hipEventRecord(p->done, s), "record completion");
     return EL_OK;
-}
+} EL_CATCH
 
-el_status el_adjoint(el_plan p, const double *y, void *p_adj, void *stream) {
+el_status el_adjoint(el_plan p, const double *y, void *p_adj, void *stream) try {
     el_status st = check_plan(p);
     if (st != EL_OK) return st;
     if ((!y && p->nrec > 0) || !p_adj) return fail(EL_EINVAL, "y or p_adj is NULL");
@@ -1202,7 +1195,7 @@ el_status el_adjoint(el_plan p, const double *y, void *p_adj, void *stream) {
     if (st != EL_OK) return st;
     HIP_TRY(hipEventRecord(p->done, s), "record completion");
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_eir_apply(const double *h, int32_t nh, const double *in, double *out, int32_t nsteps, int32_t nrec,
                        int32_t transpose, void *stream) {
@@ -1258,7 +1251,7 @@ el_status el_plan_layout(el_plan p, int64_t *row_pitch, int64_t *plane_pitch, in
     return EL_OK;
 }
 
-el_status el_plan_fluid_path(el_plan p, int32_t enable, el_fluid_stats *stats) {
+el_status el_plan_fluid_path(el_plan p, int32_t enable, el_fluid_stats *stats) try {
     el_status st = check_plan(p);
     if (st != EL_OK) return st;
     if (enable != -1 && enable != 0 && enable != 1) return fail(EL_EINVAL, "enable must be -1, 0 or 1");
@@ -1279,7 +1272,7 @@ el_status el_plan_fluid_path(el_plan p, int32_t enable, el_fluid_stats *stats) {
         }
     }
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_plan_relaxation(el_plan p, int64_t *tiles, int64_t *cells, int64_t *points) {
     if (!p) return fail(EL_EINVAL, "plan is NULL");

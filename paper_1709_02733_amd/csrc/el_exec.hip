@@ -223,12 +223,13 @@ el_status check_exec(el_exec ex, int slot) {
 
 extern "C" {
 
-el_status el_exec_create(el_exec *out, int32_t max_slots, int32_t chunk_steps) {
+el_status el_exec_create(el_exec *out, int32_t max_slots, int32_t chunk_steps) try {
     if (!out) return el::set_error(EL_EINVAL, "out is NULL");
     *out = nullptr;
     if (max_slots < 1 || max_slots > 64) return el::set_error(EL_EINVAL, "max_slots must be in 1..64");
     if (chunk_steps < 1) return el::set_error(EL_EINVAL, "chunk_steps must be >= 1");
-    el_exec ex = new el_exec_();
+    std::unique_ptr<el_exec_, el_status (*)(el_exec)> own(new el_exec_(), el_exec_destroy);   // until it is whole
+    el_exec ex = own.get();
     ex->chunk = chunk_steps;
     hipError_t e = hipGetDevice(&ex->device);
     ex->slots.resize(max_slots);
@@ -237,13 +238,10 @@ el_status el_exec_create(el_exec *out, int32_t max_slots, int32_t chunk_steps) {
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.ready, hipEventDisableTiming);
     }
-    if (e != hipSuccess) {
-        el_exec_destroy(ex);
-        return hipf(e, "executor set-up");
-    }
-    *out = ex;
+    if (e != hipSuccess) return hipf(e, "executor set-up");
+    *out = own.release();
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_exec_destroy(el_exec ex) {
     if (!ex) return EL_OK;
@@ -342,7 +340,7 @@ el_status el_exec_pump(el_exec ex) {
     return EL_OK;
 }
 
-el_status el_exec_set_ahead(el_exec ex, int32_t replays) {
+el_status el_exec_set_ahead(el_exec ex, int32_t replays) try {
     if (!ex) return el::set_error(EL_EINVAL, "executor is NULL");
     if (replays < 0 || replays > 1024) return el::set_error(EL_EINVAL, "replays must be in 0..1024");
     for (auto &sl : ex->slots)
@@ -355,6 +353,7 @@ el_status el_exec_set_ahead(el_exec ex, int32_t replays) {
         sl.head = sl.count = 0;
     }
     for (auto &sl : ex->slots) {
+        sl.ring.reserve(replays);
         for (int n = 0; n < replays; ++n) {
             hipEvent_t e = nullptr;
             EX_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming), "replay events");
@@ -363,7 +362,7 @@ el_status el_exec_set_ahead(el_exec ex, int32_t replays) {
     }
     ex->ahead = replays;
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_exec_slots(el_exec ex, int32_t *total, int32_t *busy) {
     if (!ex) return el::set_error(EL_EINVAL, "executor is NULL");

@@ -191,12 +191,13 @@ void release(Member &mb) {
 
 extern "C" {
 
-el_status el_group_create(el_group *out, int32_t max_members, int32_t precision) {
+el_status el_group_create(el_group *out, int32_t max_members, int32_t precision) try {
     if (!out) return el::set_error(EL_EINVAL, "out is NULL");
     *out = nullptr;
     if (max_members < 1 || max_members > 64) return el::set_error(EL_EINVAL, "max_members must be in 1..64");
     if (precision != EL_F32 && precision != EL_F64) return el::set_error(EL_EINVAL, "precision must be EL_F32 or EL_F64");
-    el_group g = new el_group_();
+    std::unique_ptr<el_group_, el_status (*)(el_group)> own(new el_group_(), el_group_destroy);   // until it is whole
+    el_group g = own.get();
     g->precision = precision;
     hipError_t e = hipGetDevice(&g->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking);
@@ -204,13 +205,10 @@ el_status el_group_create(el_group *out, int32_t max_members, int32_t precision)
     g->m.resize(max_members);
     for (auto &mb : g->m)
         if (e == hipSuccess) e = hipEventCreateWithFlags(&mb.done, hipEventDisableTiming);
-    if (e != hipSuccess) {
-        el_group_destroy(g);
-        return hipf(e, "group set-up");
-    }
-    *out = g;
+    if (e != hipSuccess) return hipf(e, "group set-up");
+    *out = own.release();
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_group_destroy(el_group g) {
     if (!g) return EL_OK;
@@ -265,7 +263,7 @@ el_status el_group_add(el_group g, el_plan plan, int32_t op, const void *in, voi
     return EL_OK;
 }
 
-el_status el_group_run(el_group g, int32_t ticks) {
+el_status el_group_run(el_group g, int32_t ticks) try {
     el_status st = check_group(g);
     if (st != EL_OK) return st;
     if (ticks < 0) return el::set_error(EL_EINVAL, "ticks must be >= 0");
@@ -275,6 +273,7 @@ el_status el_group_run(el_group g, int32_t ticks) {
         (void)hipEventDestroy(g->runs.front());
         g->runs.erase(g->runs.begin());
     }
+    g->runs.reserve(g->runs.size() + 1);
     for (int t = 0; t < ticks; ++t) {
         bool any = false;
         for (auto &mb : g->m) any = any || mb.running;
@@ -284,10 +283,10 @@ el_status el_group_run(el_group g, int32_t ticks) {
     }
     hipEvent_t e = nullptr;
     GR_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming), "run event");
-    g->runs.push_back(e);
+    g->runs.push_back(e);   // (room kept above)
     GR_TRY(hipEventRecord(e, g->stream), "record run end");
     return EL_OK;
-}
+} EL_CATCH
 
 el_status el_group_sync(el_group g, int32_t pending) {
     el_status st = check_group(g);

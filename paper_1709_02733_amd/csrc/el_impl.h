@@ -19,7 +19,9 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <exception>
 #include <memory>
+#include <new>
 #include <utility>
 #include <vector>
 
@@ -42,6 +44,15 @@ Vol make_vol(int nx, int ny, int nz);
 
 // Record the detail of a failure for el_last_error() and return the status.
 el_status set_error(el_status st, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
+
+// Ends an entry point of the ABI that allocates host memory, as a function-try-block: no exception
+// crosses the interface.
+#define EL_CATCH                                                              \
+    catch (const std::bad_alloc &) {                                          \
+        return el::set_error(EL_ENOMEM, "host memory ran out");               \
+    } catch (const std::exception &e) {                                       \
+        return el::set_error(EL_EDEVICE, "unexpected failure: %s", e.what()); \
+    }
 
 constexpr int kNoPml = -8;
 

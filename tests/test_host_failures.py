@@ -139,3 +139,80 @@ def test_a_failed_creation_leaves_nothing_behind(host):
         assert host.handles() == before
         n += 1
     assert n > 10 and host.handles() == before
+
+
+def _each_failed_allocation(host, call, check):
+    """call() with its 0th, 1st, ... allocation failing until it makes no more: it returns EL_ENOMEM
+    each time (an exception that left it would end the process) and check() holds after it."""
+    n = 0
+    while True:
+        host.fail_new(n)
+        st = call()
+        reached = host.news() > n
+        host.fail_new(-1)
+        if not reached:
+            return n, st
+        assert st == el.EL_ENOMEM
+        check()
+        n += 1
+
+
+def test_no_exception_leaves_the_plan_entry_points(host):
+    before = host.handles()
+    p = Plan(host)
+
+    def nothing():
+        assert not p.h.value and host.handles() == before
+
+    n, st = _each_failed_allocation(host, p.create, nothing)
+    assert st == el.EL_OK and n > 10
+    on, off = _tables_of_both(host)
+
+    def as_it_was():
+        assert p.tables() == on
+
+    n, st = _each_failed_allocation(host, lambda: p.fluid(0), as_it_was)
+    assert st == el.EL_OK and n > 4 and p.tables() == off
+    for call in (p.forward, p.adjoint):   # the events of the timed launches
+        assert host.el_plan_timing(p.h, 1) == el.EL_OK
+        assert _each_failed_allocation(host, call, lambda: None)[1] == el.EL_OK
+    p.destroy()
+    assert host.handles() == before
+
+
+def test_no_exception_leaves_the_executor_and_the_group(host):
+    before = host.handles()
+    p = Plan(host)
+    assert p.create() == el.EL_OK
+    held = host.handles()
+    ex, g, slot = vp(None), vp(None), ctypes.c_int32(-1)
+
+    def nothing():
+        assert host.handles() == held
+
+    n, st = _each_failed_allocation(host, lambda: host.el_exec_create(ctypes.byref(ex), 3, 4), nothing)
+    assert st == el.EL_OK and n >= 2
+    assert _each_failed_allocation(host, lambda: host.el_exec_set_ahead(ex, 5), lambda: None)[1] == el.EL_OK
+    n, st = _each_failed_allocation(
+        host, lambda: host.el_exec_start(ex, p.h, el.OP_FORWARD, vp(p.image.ctypes.data), vp(p.traces.ctypes.data), None,
+                                         ctypes.byref(slot)), lambda: None)
+    assert st == el.EL_OK and host.el_exec_wait(ex, slot) == el.EL_OK
+    assert host.el_exec_destroy(ex) == el.EL_OK
+    nothing()
+    n, st = _each_failed_allocation(host, lambda: host.el_group_create(ctypes.byref(g), 3, el.EL_F32), nothing)
+    assert st == el.EL_OK and n >= 2
+    n, st = _each_failed_allocation(
+        host, lambda: host.el_group_add(g, p.h, el.OP_ADJOINT, vp(p.traces.ctypes.data), vp(p.image.ctypes.data), None,
+                                        ctypes.byref(slot)), lambda: None)
+    assert st == el.EL_OK
+    steps = ctypes.c_int32(0)
+
+    def no_half_step():
+        assert host.el_group_poll(g, slot, ctypes.byref(steps), None) == el.EL_OK and steps.value in (0, 2)
+
+    n, st = _each_failed_allocation(host, lambda: host.el_group_run(g, 2), no_half_step)
+    assert st == el.EL_OK and n >= 2
+    assert host.el_group_destroy(g) == el.EL_OK
+    nothing()
+    p.destroy()
+    assert host.handles() == before
