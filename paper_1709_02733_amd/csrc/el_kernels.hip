@@ -407,10 +407,11 @@ hipError_t launch_extract(const Dev<T> &d, T *p, hipStream_t s) {
 //
 // Bound by the loads: with a thread per sample every tap cost a load of 8 bytes per lane for one
 // multiply-add.  Here a window of 2 R - 1 inputs stays in registers and serves R taps of R samples,
-// so a load serves R multiply-adds, and the next R inputs are in flight meanwhile; the taps are
-// scalar loads.  Each sample adds its terms in the order of k, as a loop over k does.  EDGE: some
-// samples or taps of this wavefront lie outside the trace (inputs are read at the nearest sample
-// and their terms left out).
+// so a load serves R multiply-adds; the taps are scalar loads.  (The next R inputs are asked for
+// ahead of the taps, but under a condition, so the first multiply-add waits for them.)  Each sample
+// adds its terms in the order of k, as a loop over k does.  EDGE: some samples or taps of this
+// wavefront lie outside the trace (inputs are read at the nearest sample and their terms left out);
+// it stops at the last tap that has a term.
 template <int R, bool TR, bool EDGE>
 __device__ __forceinline__ void eir_samples(const double *h, int nh, const double *in, double *out, int M, int L,
                                             int l, int m0) {
@@ -419,6 +420,7 @@ __device__ __forceinline__ void eir_samples(const double *h, int nh, const doubl
     auto at = [&](int m) { return in[(size_t)(EDGE ? max(0, min(m, M - 1)) : m) * L + lane]; };
     // taps k0 .. k0 + R - 1 of samples m0 .. m0 + R - 1 take inputs first(k0) .. first(k0) + 2 R - 2
     auto first = [&](int k0) { return TR ? m0 + k0 : m0 - k0 - (R - 1); };
+    if (EDGE) nh = min(nh, TR ? M - m0 : m0 + R);
     double acc[R] = {}, w[2 * R - 1], next[R];
 #pragma unroll
     for (int j = 0; j < 2 * R - 1; ++j) w[j] = at(first(0) + j);
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(256) void k_eir(const double *h, int nh, const doub
 template <int R>
 hipError_t launch_eir_r(const double *h, int nh, const double *in, double *out, int M, int L, int transpose,
                         hipStream_t s) {
-    const long long blocks = (long long)((L + 63) / 64) * ((M + 4 * R - 1) / (4 * R));   // < 2^31 (checked by the caller)
+    const long long blocks = ((L + 63ll) / 64) * ((M + 4ll * R - 1) / (4 * R));   // < 2^31 (checked by the caller)
     if (transpose) hipLaunchKernelGGL((k_eir<R, true>), dim3((unsigned)blocks), dim3(256), 0, s, h, nh, in, out, M, L);
     else hipLaunchKernelGGL((k_eir<R, false>), dim3((unsigned)blocks), dim3(256), 0, s, h, nh, in, out, M, L);
     return hipGetLastError();
@@ -475,11 +477,12 @@ hipError_t launch_eir_r(const double *h, int nh, const double *in, double *out, 
 hipError_t launch_eir(const double *h, int nh, const double *in, double *out, int M, int L, int transpose,
                       hipStream_t s) {
     if (M == 0 || L == 0) return hipSuccess;
+    nh = std::min(nh, M);   // no sample has a term of a later tap
     // 8 samples per thread where that leaves two wavefronts per SIMD, else 4.  Measured (samples x
     // receivers, taps; us at one sample per thread as it was, then at 2, 4, 8, 12 and 16):
     // 2500 x 1024, 171: 213, 124, 75, 45, 55, 59; 3000 x 1024, 400: 538, 349, 171, 97, 98, 120;
     // 1000 x 512, 171: 48, 29, 22, 24, 38, 49; 2500 x 128, 171: 25, 24, 20, 23, 37, 48.
-    const long long wavefronts = (long long)((L + 63) / 64) * ((M + 7) / 8);
+    const long long wavefronts = ((L + 63ll) / 64) * ((M + 7ll) / 8);
     if (wavefronts >= 2048) return launch_eir_r<8>(h, nh, in, out, M, L, transpose, s);
     return launch_eir_r<4>(h, nh, in, out, M, L, transpose, s);
 }
