@@ -124,6 +124,11 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
 constexpr int kZChunk = 6;
 constexpr long long kMinTiles = 4096;
 constexpr int kMaxTiles = (1 << 24) - 1;   // (arrays below 4 GiB keep under it)
+// The Infinity Cache: a state of less is still there when the next pass reads it (ld_own).  By the
+// bytes that a step touches the hint loses 17 to 24% at 126 to 188 MiB (shells of 160^3 and, in double
+// precision, 144^3), 7% at 228 (solid 152^3), and gains 5% at 248 (shell of 208^3) and 4% at 263 (solid
+// 160^3).
+constexpr long long kStreamBytes = 256ll << 20;
 constexpr long long kFewBlocks = 5120, kManyBlocks = 10240;   // see block_planes
 int chunk_planes(int nx, int ny, int nz) {
     const long long cols = (long long)((nx + kTileX - 1) / kTileX) * ((ny + kTileY - 1) / kTileY);
@@ -142,6 +147,7 @@ Tiles make_tiles(int nx, int ny, int nz) {
     t.ntiles = t.ntx * t.nty * t.nzc;
     t.order = nullptr;
     t.per = t.cap = 0;
+    t.once = false;
     // an XCD's entries at most: four per piece.  The pieces of a tile column are at least two planes
     // apart but for a last one; with blocks of kZBlock at least and runs of kZChunk planes (every
     // plane of a tile column is in an entry, so block_planes counts cols nz planes or more) a run of
@@ -173,7 +179,7 @@ Tiles make_tiles(int nx, int ny, int nz) {
 // so fewer taps miss its L2.  Measured (us per forward / adjoint step, bands and boxes): skull
 // medium 48^3 12.2/12.5 and 11.7/12.1, 64^3 14.1/15.5 and 13.3/14.8, 96^3 26.8/29.5 and 26.6/29.1,
 // 112^3 36.2/39.9 and 36.4/40.5, 128^3 41.8/46.6 and 42.7/47.8, 192^3 116.9/125.7 and 123.1/133.2,
-// 288^3 373/387 and 393/408; soft tissue 64^3 11.0/11.0 and 10.6/10.9, 96^3 17.4/17.8 and
+// 288^3 365/385 and 387/408; soft tissue 64^3 11.0/11.0 and 10.6/10.9, 96^3 17.4/17.8 and
 // 16.8/17.5, 128^3 31.4/33.2 and 32.4/34.0, 208^3 138/144 and 144/151.  On large grids the bands
 // win: every XCD is at the same planes at the same time, and carries the same mix of updates.
 int piece_xcd(const Tiles &t, int by, int z, long long index) {
@@ -236,33 +242,55 @@ Subs subs_of(const Tiles &t, int nx, int ny, const unsigned char *fast, const un
 // are): skull medium 64^3 (900) 13.5/14.8, 14.6/15.4, 16.7/17.3; 96^3 (2800)
 // 26.6/29.6, 27.4/29.4, 32.9/35.1; 128^3 (5000) 42.3/47.2, 43.2/47.8, 44.4/48.5; 136^3 (6700)
 // 47.3/51.8, 48.9/52.2, 48.0/51.5; 152^3 (8700) 60.3/70.3, 56.4/61.9, 56.1/59.5; 192^3 124/140, 118/130,
-// 116/124; 384^3 815/909, 804/841, 803/831 (6 planes 807/836); soft tissue 112^3 24.0/25.9,
+// 116/124; 384^3 818/915, 785/842, 771/811 (6 planes 773/808); soft tissue 112^3 24.0/25.9,
 // 25.9/27.5, 24.4/25.9; 144^3 (3888) 41.6/44.1, 42.8/44.8, 43.2/44.8; all solid 48^3 13.0/13.4,
 // 13.4/13.7, 15.0/15.1; 80^3 (3200) 26.3/28.3, 25.9/27.6, 26.6/27.6; 112^3 (6272) 50.2/56.7,
 // 50.0/53.9, 48.5/52.6; 128^3 skull in double precision 77.5/92.3, 79.2/93.8, 79.6/95.1.
 // Mostly solid, 4, 6, 8 and 12 planes: 157 x 131 x 109 (5500 blocks of 8) 65.2/70.5, 68.2/72.8,
-// 67.6/73.6, 76.4/80.3; 203 x 187 x 150 (14288) 223/251, 222/251, 220/250, 225/254; 256^3 564/611,
-// 554/601, 558/601, 561/605; 384^3 1760/1886, 1731/1846, 1721/1829, 1719/1823; 192^3 in double
-// precision (13824) 545/612, 534/599, 532/596, 540/598.
-int block_planes(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes) {
+// 67.6/73.6, 76.4/80.3; 203 x 187 x 150 (14288) 210/232, 211/232, 209/232, 214/235; 256^3 550/598,
+// 541/587, 544/587, 547/591; 320^3 1028/1108, 1007/1082, 1006/1079, 1004/1077; 384^3 1725/1851,
+// 1691/1805, 1680/1790, 1680/1785; 192^3 in double precision (13824) 531/599, 521/586, 518/582, 525/584.
+int block_planes(const Tiles &t, int nx, int ny, int P, const unsigned char *fast, const unsigned char *uni,
+                 const unsigned long long *lanes, long long *touched) {
     long long planes = 0;        // over the entries
     long long subs = 0, general = 0;   // sub-tiles
+    // elements of the state that a time step touches, by kind of sub-tile: all nine fields and four maps
+    // (general), u, s11 and three maps (fluid) or none of the maps (uniform); of every layer that a cell
+    // is in, the six memory variables of its axis (general) or the two diagonal ones
+    long long state = 0;
+    auto layers = [P](int c0, int c1, int n) {
+        return P <= 0 ? 0ll : (long long)std::max(0, std::min(c1, P + 1) - c0) + std::max(0, c1 - std::max(c0, n - 1 - P));
+    };
     int q = 0;
     for (int bz = 0; bz < t.nzc; ++bz) {
-        const int depth = std::min(t.zc, t.nz - bz * t.zc);
+        const int z0 = bz * t.zc, z1 = std::min(z0 + t.zc, t.nz), depth = z1 - z0;
         for (int by = 0; by < t.nty; ++by)
             for (int bx = 0; bx < t.ntx; ++bx, ++q) {
+                auto add = [&](int x0, int w, int y0, int h, int arrays, int memory) {
+                    w = std::min(w, nx - x0);
+                    h = std::min(h, ny - y0);
+                    state += (long long)w * h * depth * arrays +
+                             memory * (layers(x0, x0 + w, nx) * h * depth + layers(y0, y0 + h, ny) * w * depth + layers(z0, z1, t.nz) * w * h);
+                };
                 if (fast && fast[q]) {
                     planes += depth;
                     subs += 4;
+                    add(bx * kTileX, kTileX, by * kTileY, kTileY, uni[q] ? 4 : 7, 2);
                     continue;
                 }
                 const Subs u = subs_of(t, nx, ny, fast, lanes, bx, by, q);
                 planes += u.entries() * depth;
                 subs += __builtin_popcount(u.in);
                 general += __builtin_popcount(u.in & ~u.fluid);
+                for (int s = 0; s < 4; ++s)
+                    if (u.in >> s & 1u) {
+                        const bool fl = u.fluid >> s & 1u;
+                        add(bx * kTileX + (s & 1) * kWaveX, kWaveX, by * kTileY + (s >> 1) * kWaveY, kWaveY,
+                            !fl ? NFIELD + 4 : (u.same >> s & 1u ? 4 : 7), fl ? 2 : 6);
+                    }
             }
     }
+    *touched = state;
     if (planes < kFewBlocks * kZBlock) return 2;
     return 4 * general >= 3 * subs && planes >= kManyBlocks * kZDeep ? kZDeep : kZBlock;
 }
@@ -378,9 +406,11 @@ template <typename T>
 BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
                         const unsigned long long *lanes, const T *med, const std::vector<int> &points) {
     Tiles t = tiles;
-    t.zb = block_planes(t, nx, ny, fast, lanes);
-    // room for cap entries per XCD (an entry costs its 64 bytes only once it is written)
+    long long touched = 0;
+    t.zb = block_planes(t, nx, ny, npml, fast, uni, lanes, &touched);
     BlockList<T> out;
+    out.once = touched * (long long)sizeof(T) > kStreamBytes;
+    // room for cap entries per XCD (an entry costs its 64 bytes only once it is written)
     out.entries.reset(new BlockEnt<T>[8 * (size_t)t.cap]);
     BlockEnt<T> *order = out.entries.get();
     size_t count[8] = {};
@@ -808,12 +838,14 @@ el_status set_tables_t(el_plan p, Dev<T> &d, bool fluid, hipStream_t s) {
                     "increments");
         }
         HIP_TRY(hipStreamSynchronize(s), "block list");
+        p->once[on] = list.once;
         p->per[on] = list.per;
     }
     d = nd;
     p->rec.fl = reinterpret_cast<unsigned char *>(ws + p->L.rec_fl[on]);
     p->rec.pos = reinterpret_cast<int *>(ws + p->L.csr_pos[on]);
     p->tiles.order = ws + p->L.tile_order[on];
+    p->tiles.once = p->once[on];
     p->tiles.per = p->per[on];
     p->fluid_path = fluid;
     return EL_OK;

@@ -184,6 +184,7 @@ struct Tiles {
     int ntiles;              // ntx * nty * nzc
     int cap;                 // entries per XCD at most
     int per;                 // entries per XCD: the grid has 8 * per blocks
+    bool once;               // the state outgrows the Infinity Cache (kStreamBytes)
     const void *order;       // device: the block list (BlockEnt<T>); entry b is block b's, on XCD b % 8
 };
 Tiles make_tiles(int nx, int ny, int nz);
@@ -199,6 +200,7 @@ struct BlockList {
     std::unique_ptr<BlockEnt<T>[]> entries;
     bool fits = true;        // false: an XCD's entries outgrow their room, and there is no list
     int per = 0;
+    bool once = false;       // Tiles::once
     long long planes = 0;    // increment planes of kWaveX x kWaveY elements
     std::vector<int> pos;    // each point's element in them
 };
@@ -447,6 +449,7 @@ struct el_plan_ {
     long long fast_skipped = 0;        // s22 and s33 stores a fluid stress pass leaves out
     std::vector<int> rec_tile;         // [L][8] tile of each receiver corner (host)
     std::vector<int> points;           // i, j, k of the scatter points (host)
+    bool once[2] = {};                 // Tiles::once and
     int per[2] = {};                   // Tiles::per of the tables without, with the fluid update (0: not made yet)
     bool fluid_path = true;            // use the fluid update where it applies
     hipEvent_t done;

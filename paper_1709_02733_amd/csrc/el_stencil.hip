@@ -64,10 +64,13 @@
 //
 // Measured (MI355X, us per forward and adjoint step together, with a wavefront per sub-tile and now;
 // "adjoint": that step alone): skull medium 64^3 42.1 to 27.7, 96^3 adjoint 41.9 to 29.6, 128^3
-// 101.9 to 89.4, 128^3 in double precision 197 to 169, 256^3 636 to 565, 384^3 1639 to 1635;
-// all solid 157 x 131 x 109 141 to 137, 203 x 187 x 150 549 to 471, 256^3 1188 to 1158, but 384^3
-// 3472 to 3555, where the passes are bound by memory and a sub-tile's y halo is no longer shared
-// in L1 with the tile's other sub-tiles.
+// 101.9 to 89.4, 128^3 in double precision 197 to 169, 256^3 636 to 540, 384^3 1640 to 1583;
+// all solid 157 x 131 x 109 141 to 137, 203 x 187 x 150 549 to 442, 256^3 1188 to 1132, 320^3 2106 to
+// 2086, 384^3 3474 to 3471 (without layers 2953 to 3039).  On the largest grids the split itself
+// loses: a sub-tile's halo is no longer shared in L1 with the tile's other sub-tiles, the passes ask
+// L2 for 10 to 13% more lines (384^3, TCC_REQ) and the lines in flight bound them.  Blocks of two or
+// four sub-tiles share the halo and lose more, waiting for 8 or 16 free wavefronts (384^3 solid
+// 1801/1911 to 1882/2064 and 2076/2557 us); ld_own makes up for it.
 #include "el_impl.h"
 
 namespace el {
@@ -188,6 +191,31 @@ __device__ __forceinline__ void stb(Arr<T> base, unsigned off, T v) {
 template <typename T>
 __device__ __forceinline__ T ldi(Arr<T> base, unsigned off, int elements) {
     return *((Arr<T>)((Arr<char>)base + off) + elements);
+}
+// The same for an old and a new value of a field, which one lane reads and writes and no other reads
+// in this pass.  ONCE: with a hint that it need not stay in the caches, so that it does not take the
+// place of taps there.
+//
+// Where the state outgrows the Infinity Cache that is what the general update gains from: with
+// several wavefronts per sub-tile its taps ask L2 for 10 to 13% more lines than one wavefront for all
+// of a sub-tile did, and L1 holds fewer of them.  Where the state fits the next pass reads the value
+// from that cache, and the hint costs more than it gives.  Measured (us per forward / adjoint step,
+// without and with it): all solid 128^3 66.9/74.3 and 81.3/86.9, 152^3 118/134 and 127/141, 160^3
+// 156/166 and 150/160, 192^3 262/286 and 251/268, 320^3 1066/1136 and 1038/1109, 384^3 1801/1911 and
+// 1753/1865; a thin shell in water 160^3 64/66 and 77/81, 192^3 110/120 and 118/123, 208^3 157/171
+// and 152/159, 256^3 278/290 and 266/283; in double precision solid 112^3 95/112 and 130/146, 128^3
+// 181/207 and 178/198, shell 144^3 100/116 and 123/137, 160^3 162/185 and 166/180.  See
+// kStreamBytes for the line.
+template <typename T, bool ONCE>
+__device__ __forceinline__ T ld_own(Arr<T> base, unsigned off) {
+    Arr<T> a = (Arr<T>)((Arr<char>)base + off);
+    return ONCE ? __builtin_nontemporal_load(a) : *a;
+}
+template <typename T, bool ONCE>
+__device__ __forceinline__ void st_own(Arr<T> base, unsigned off, T v) {
+    Arr<T> a = (Arr<T>)((Arr<char>)base + off);
+    if (ONCE) __builtin_nontemporal_store(v, a);
+    else *a = v;
 }
 // The four samples from t0 to t0 + 3 cells along axis A.
 template <typename T, int A>
@@ -406,7 +434,7 @@ __device__ __forceinline__ void fluid_vel(const Dev<T> &d, int i, int j, int z0,
 // so are the off-diagonal memory variables that act on it); mp: it reads rho and alpha from the
 // maps.  s22 and s33 hold s11's value on a fluid lane's taps (fluid columns store all three,
 // fluid tiles the bands next to general tiles).
-template <typename T, bool ADJ, bool EN, int C>
+template <typename T, bool ADJ, bool EN, bool ONCE, int C>
 __device__ __forceinline__ void gen_vel(const Dev<T> &d, int i, int j, int z0, int z1, unsigned o, bool sh, bool mp,
                                         T rho_t, T alp_t, double &kin) {
     const T h = d.inv_dx, dt = d.dt;
@@ -443,7 +471,7 @@ __device__ __forceinline__ void gen_vel(const Dev<T> &d, int i, int j, int z0, i
             if (C != 1) taps<T, 1>(fy, o, t0[1], st[1], tap[1]);
             if (C != 2) qn = ldb<T>(fz, o + (unsigned)(t0[2] + 3) * st[2]);
         }
-        const T uold = ldb<T>(u, o);
+        const T uold = ld_own<T, ONCE>(u, o);
         if (mp) {
             if (C < 2) {
                 rho_k = ldb<T>(rho, o);
@@ -488,7 +516,7 @@ __device__ __forceinline__ void gen_vel(const Dev<T> &d, int i, int j, int z0, i
         const T irho = rcp(rho_c);
         const T J = fma(-dt, alp_c, T(1));
         const T out = ADJ ? fma(uold, J, -(acc * irho)) : fma(acc, dt * irho, uold * J);
-        stb<T>(u, o, out);
+        st_own<T, ONCE>(u, o, out);
         if (EN) kin = fma((double)rho_c * (double)uold, (double)out, kin);
         if (C == 2) {
             rho_k = rho_n;
@@ -531,8 +559,10 @@ __device__ __forceinline__ double block_sum(double v) {
 // *ctr of the traces at row, the scatter blocks read row *ctr - 1 (the stress pass that follows
 // advances the counter, or steps it back).
 //
+// ONCE: see ld_own.
+//
 // G > 1 (grouped launch): the blocks of member q of the group are first[q] .. first[q+1]-1.
-template <typename T, bool ADJ, bool EN, int G>
+template <typename T, bool ADJ, bool EN, bool ONCE, int G>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 1))) void k_vel(Grp<T, G> g,
                                                                                               double *epart, int *ctr) {
     static_assert(NT == 256, "gather_block works on blocks of 256 threads");
@@ -566,9 +596,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
             } else {
                 bool fl, ul;
                 fluid_lanes(b, fl, ul);
-                if (w == 0) gen_vel<T, ADJ, EN, 0>(d, i, j, b.z0, b.z1, o, !fl, !ul, b.rho, b.alpha, kin);
-                else if (w == 1) gen_vel<T, ADJ, EN, 1>(d, i, j, b.z0, b.z1, o, !fl, !ul, b.rho, b.alpha, kin);
-                else gen_vel<T, ADJ, EN, 2>(d, i, j, b.z0, b.z1, o, !fl, !ul, b.rho, b.alpha, kin);
+                if (w == 0) gen_vel<T, ADJ, EN, ONCE, 0>(d, i, j, b.z0, b.z1, o, !fl, !ul, b.rho, b.alpha, kin);
+                else if (w == 1) gen_vel<T, ADJ, EN, ONCE, 1>(d, i, j, b.z0, b.z1, o, !fl, !ul, b.rho, b.alpha, kin);
+                else gen_vel<T, ADJ, EN, ONCE, 2>(d, i, j, b.z0, b.z1, o, !fl, !ul, b.rho, b.alpha, kin);
             }
         }
     }
@@ -592,7 +622,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 // (psi^{cc}; in the adjoint a phi~^{cc} and a psi~^{cc}) belong to the normal stresses.  inc
 // (adjoint, null without scatter points): the sub-tile's increments of Theta^T y (scatter_value),
 // which times 3 lambda + 2 mu are added to all three.
-template <typename T, bool ADJ, bool FLUID, bool UNI>
+template <typename T, bool ADJ, bool FLUID, bool UNI, bool ONCE>
 __device__ __forceinline__ void normal_str(const Dev<T> &d, int i, int j, int z0, int z1, unsigned o, T lam_t, bool sh,
                                            bool ul, bool put22, int zlo, int zhi, const T *inc) {
     const T h = d.inv_dx, dt = d.dt;
@@ -618,10 +648,10 @@ __device__ __forceinline__ void normal_str(const Dev<T> &d, int i, int j, int z0
         const T qn = ldb<T>(u3, o + st[2]);
         taps<T, 0>(u1, o, -2, st[0], tap[0]);
         taps<T, 1>(u2, o, -2, st[1], tap[1]);
-        sold[0] = ldb<T>(s[0], o);
+        sold[0] = ld_own<T, ONCE>(s[0], o);
         if (!FLUID && sh) {
-            sold[1] = ldb<T>(s[1], o);
-            sold[2] = ldb<T>(s[2], o);
+            sold[1] = ld_own<T, ONCE>(s[1], o);
+            sold[2] = ld_own<T, ONCE>(s[2], o);
             mu = ldb<T>(mup, o);
         }
         if (!UNI && !ul) lam = ldb<T>(lamp, o);
@@ -665,7 +695,7 @@ __device__ __forceinline__ void normal_str(const Dev<T> &d, int i, int j, int z0
             for (int c = 0; c < 3; ++c) {
                 const T so = c == 0 || sh ? sold[c] : sold[0], de = fma(mu + mu, e[c], lt);
                 w[c] = ADJ ? so - de : fma(dt, de, so);
-                stb<T>(s[c], o, ADJ ? fma(kf, add, w[c]) : w[c]);
+                st_own<T, ONCE>(s[c], o, ADJ ? fma(kf, add, w[c]) : w[c]);
             }
         }
         if (ADJ) {
@@ -683,7 +713,7 @@ __device__ __forceinline__ void normal_str(const Dev<T> &d, int i, int j, int z0
 
 // Shear stress sigma^{AB} (A < B) of a general column, one wavefront per shear stress.  Lanes of
 // fluid columns do not come here: their shear stresses stay zero.
-template <typename T, bool ADJ, int A, int B>
+template <typename T, bool ADJ, bool ONCE, int A, int B>
 __device__ __forceinline__ void shear_str(const Dev<T> &d, int i, int j, int z0, int z1, unsigned o) {
     static_assert(A < B, "axes in order");
     const T h = d.inv_dx, dt = d.dt;
@@ -718,7 +748,7 @@ __device__ __forceinline__ void shear_str(const Dev<T> &d, int i, int j, int z0,
             muA = ldb<T>(mu, o + st[A]);
         }
         taps<T, A>(ub, o, -1, st[A], tb);
-        const T sold = ldb<T>(s, o);
+        const T sold = ld_own<T, ONCE>(s, o);
         const T muB = ldb<T>(mu, o + st[B]), muAB = ldb<T>(mu, o + st[A] + st[B]);
         sl.template ld<A>(moA, true, ownA);
         sl.template ld<B>(moB, true, ownB);
@@ -759,7 +789,7 @@ __device__ __forceinline__ void shear_str(const Dev<T> &d, int i, int j, int z0,
             muA = muAB;
         }
         const T w = fma(ADJ ? -m : dt * m, eB + eA, sold);
-        stb<T>(s, o, w);
+        st_own<T, ONCE>(s, o, w);
         if (ADJ) {
             if (sl.own[A]) sl.template put<A>(moA, fma(pb[A], ownA, pa[A] * dt * w));
             if (sl.own[B]) sl.template put<B>(moB, fma(pb[B], ownB, pa[B] * dt * w));
@@ -775,8 +805,8 @@ __device__ __forceinline__ void shear_str(const Dev<T> &d, int i, int j, int z0,
 //
 // ctr (captured step graphs): the pass advances (the adjoint steps back) the device step counter
 // that its velocity pass's extra blocks read (all of that launch has completed).  G > 1: grouped
-// launch, as k_vel.
-template <typename T, bool ADJ, int G>
+// launch, as k_vel.  ONCE: see ld_own.
+template <typename T, bool ADJ, bool ONCE, int G>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 1))) void k_str(Grp<T, G> g, int *ctr) {
     const int q = member_of(g);
     const int bid = G > 1 ? (int)blockIdx.x - g.first[q] : (int)blockIdx.x;
@@ -806,18 +836,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         const bool put22 = keep || ((ed & 1) && j < b.y0 + 2) || ((ed & 2) && j >= b.y0 + TY - 2);
         const int zlo = keep ? b.z1 : ((ed & 4) ? b.z0 + 2 : b.z0), zhi = keep ? b.z0 : ((ed & 8) ? b.z1 - 2 : b.z1);
         const bool uni = ((b.fl >> (kBlkUniShift + w)) & 1u) != 0;
-        if (uni) normal_str<T, ADJ, true, true>(d, i, j, b.z0, b.z1, o, b.lam, false, true, put22, zlo, zhi, inc);
-        else normal_str<T, ADJ, true, false>(d, i, j, b.z0, b.z1, o, b.lam, false, false, put22, zlo, zhi, inc);
+        if (uni) normal_str<T, ADJ, true, true, false>(d, i, j, b.z0, b.z1, o, b.lam, false, true, put22, zlo, zhi, inc);
+        else normal_str<T, ADJ, true, false, false>(d, i, j, b.z0, b.z1, o, b.lam, false, false, put22, zlo, zhi, inc);
     } else {
         bool fl, ul;
         fluid_lanes(b, fl, ul);
         if (w == 0) {
-            normal_str<T, ADJ, false, false>(d, i, j, b.z0, b.z1, o, b.lam, !fl, ul, true, 0, 0, inc);
+            normal_str<T, ADJ, false, false, ONCE>(d, i, j, b.z0, b.z1, o, b.lam, !fl, ul, true, 0, 0, inc);
         } else {
             if (fl) return;
-            if (w == 1) shear_str<T, ADJ, 1, 2>(d, i, j, b.z0, b.z1, o);
-            else if (w == 2) shear_str<T, ADJ, 0, 2>(d, i, j, b.z0, b.z1, o);
-            else shear_str<T, ADJ, 0, 1>(d, i, j, b.z0, b.z1, o);
+            if (w == 1) shear_str<T, ADJ, ONCE, 1, 2>(d, i, j, b.z0, b.z1, o);
+            else if (w == 2) shear_str<T, ADJ, ONCE, 0, 2>(d, i, j, b.z0, b.z1, o);
+            else shear_str<T, ADJ, ONCE, 0, 1>(d, i, j, b.z0, b.z1, o);
         }
     }
 }
@@ -842,15 +872,14 @@ hipError_t launch_velocity(const Dev<T> &d, const Tiles &tl, hipStream_t s, cons
     const bool gat = r && grow && r->nrec > 0;
     const int blocks = 8 * tl.per + (gat ? gather_blocks(r->nrec) : 0);
     const Grp<T, 1> g = one<1>(d, tl, gat ? r : nullptr, gat ? grow : nullptr);
-    if (epart)
-        hipLaunchKernelGGL((k_vel<T, false, true, 1>), dim3(blocks), dim3(NT), 0, s, g, epart, ctr);
-    else
-        hipLaunchKernelGGL((k_vel<T, false, false, 1>), dim3(blocks), dim3(NT), 0, s, g, (double *)nullptr, ctr);
+    const auto plain = tl.once ? k_vel<T, false, false, true, 1> : k_vel<T, false, false, false, 1>;
+    hipLaunchKernelGGL((epart ? k_vel<T, false, true, false, 1> : plain), dim3(blocks), dim3(NT), 0, s, g, epart, ctr);
     return hipGetLastError();
 }
 template <typename T>
 hipError_t launch_stress(const Dev<T> &d, const Tiles &tl, hipStream_t s, int *ctr) {
-    hipLaunchKernelGGL((k_str<T, false, 1>), dim3(8 * tl.per), dim3(NT), 0, s, one<1>(d, tl), ctr);
+    hipLaunchKernelGGL((tl.once ? k_str<T, false, true, 1> : k_str<T, false, false, 1>), dim3(8 * tl.per), dim3(NT), 0, s,
+                       one<1>(d, tl), ctr);
     return hipGetLastError();
 }
 template <typename T>
@@ -858,26 +887,34 @@ hipError_t launch_adj_velocity(const Dev<T> &d, const Tiles &tl, hipStream_t s, 
                                int *ctr) {
     const bool sc = r && y && r->npts > 0;
     const int blocks = 8 * tl.per + (sc ? scatter_blocks(r->npts) : 0);
-    hipLaunchKernelGGL((k_vel<T, true, false, 1>), dim3(blocks), dim3(NT), 0, s,
+    hipLaunchKernelGGL((tl.once ? k_vel<T, true, false, true, 1> : k_vel<T, true, false, false, 1>), dim3(blocks), dim3(NT), 0, s,
                        one<1>(d, tl, sc ? r : nullptr, sc ? const_cast<double *>(y) : nullptr), (double *)nullptr, ctr);
     return hipGetLastError();
 }
 template <typename T>
 hipError_t launch_adj_stress(const Dev<T> &d, const Tiles &tl, hipStream_t s, int *ctr) {
-    hipLaunchKernelGGL((k_str<T, true, 1>), dim3(8 * tl.per), dim3(NT), 0, s, one<1>(d, tl), ctr);
+    hipLaunchKernelGGL((tl.once ? k_str<T, true, true, 1> : k_str<T, true, false, 1>), dim3(8 * tl.per), dim3(NT), 0, s,
+                       one<1>(d, tl), ctr);
     return hipGetLastError();
 }
 
 // Grouped passes: members q < g.n with first[] set by group_blocks.
+template <typename T, bool ONCE>
+void group_pass(const Grp<T, kGroupMax> &g, int pass, hipStream_t s) {
+    const dim3 grid(g.first[g.n]);
+    if (pass == 1 || pass == 3)
+        hipLaunchKernelGGL((pass == 1 ? k_str<T, false, ONCE, kGroupMax> : k_str<T, true, ONCE, kGroupMax>), grid, dim3(NT), 0, s,
+                           g, (int *)nullptr);
+    else
+        hipLaunchKernelGGL((pass == 0 ? k_vel<T, false, false, ONCE, kGroupMax> : k_vel<T, true, false, ONCE, kGroupMax>), grid,
+                           dim3(NT), 0, s, g, (double *)nullptr, (int *)nullptr);
+}
 template <typename T>
 hipError_t launch_group_pass(const Grp<T, kGroupMax> &g, int pass, hipStream_t s) {
-    const dim3 grid(g.first[g.n]);
-    switch (pass) {
-        case 0: hipLaunchKernelGGL((k_vel<T, false, false, kGroupMax>), grid, dim3(NT), 0, s, g, (double *)nullptr, (int *)nullptr); break;
-        case 1: hipLaunchKernelGGL((k_str<T, false, kGroupMax>), grid, dim3(NT), 0, s, g, (int *)nullptr); break;
-        case 2: hipLaunchKernelGGL((k_vel<T, true, false, kGroupMax>), grid, dim3(NT), 0, s, g, (double *)nullptr, (int *)nullptr); break;
-        default: hipLaunchKernelGGL((k_str<T, true, kGroupMax>), grid, dim3(NT), 0, s, g, (int *)nullptr); break;
-    }
+    bool once = true;   // of every member's state
+    for (int q = 0; q < g.n; ++q) once = once && g.tl[q].once;
+    if (once) group_pass<T, true>(g, pass, s);
+    else group_pass<T, false>(g, pass, s);
     return hipGetLastError();
 }
 

@@ -11,7 +11,8 @@
 using namespace el;
 
 namespace el {
-int block_planes(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes);
+int block_planes(const Tiles &t, int nx, int ny, int P, const unsigned char *fast, const unsigned char *uni,
+                 const unsigned long long *lanes, long long *touched);
 }
 
 namespace {
@@ -45,7 +46,8 @@ extern "C" {
 
 const char *check_message() { return g_msg.c_str(); }
 
-// out: planes per block, entries per XCD, room per XCD, general sub-tiles' share in per mille.
+// out: planes per block, entries per XCD, room per XCD, general sub-tiles' share in per mille, whether
+// the passes stream, elements that a step touches in thousands.
 // room > 0 replaces the room per XCD; then 2 is returned if the list does not fit it.
 int check_blocks(int nx, int ny, int nz, int npml, const unsigned char *solid, const unsigned char *medium, int fluid,
                  const int *points, int npoints, int nrec, int room, int *out) {
@@ -78,7 +80,8 @@ int check_blocks(int nx, int ny, int nz, int npml, const unsigned char *solid, c
     }
     const unsigned char *f = fluid ? fast.data() : nullptr;
     const std::vector<int> pts(points, points + 3 * (size_t)npoints);
-    out[0] = block_planes(t, nx, ny, f, lanes.data());
+    long long touched = 0;
+    out[0] = block_planes(t, nx, ny, npml, f, uni.data(), lanes.data(), &touched);
     const BlockList<float> list = block_list<float>(t, nx, ny, npml, f, uni.data(), lanes.data(), med.data(), pts);
     out[2] = t.cap;
     if (!list.fits) return 2;
@@ -180,6 +183,8 @@ int check_blocks(int nx, int ny, int nz, int npml, const unsigned char *solid, c
         if (w >= 0) planes.push_back(w);
     std::sort(planes.begin(), planes.end());
     if (std::adjacent_find(planes.begin(), planes.end()) != planes.end()) return bad("two planes share increments");
+    out[4] = list.once;
+    out[5] = (int)(touched / 1000);
     out[3] = subs ? (int)(1000 * general / subs) : 0;
     return 0;
 }

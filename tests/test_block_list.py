@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 from paper_1709_02733_amd import build as B
+from tests import large_media as LM
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -32,11 +33,11 @@ def check(tmp_path_factory):
         corners = np.array([[c & 1, c >> 1 & 1, c >> 2 & 1] for c in range(8)])
         pts = np.unique((base[:, None] + corners).reshape(-1, 3), axis=0)
         pts = np.ascontiguousarray(pts[np.lexsort((pts[:, 0], pts[:, 1], pts[:, 2]))], np.int32)
-        out = np.zeros(4, np.int32)
+        out = np.zeros(6, np.int32)
         ptr = [a.ctypes.data_as(ctypes.c_void_p) for a in (solid, medium, pts, out)]
         rc = lib.check_blocks(nx, ny, nz, npml, ptr[0], ptr[1], int(fluid), ptr[2], len(pts), nrec, room, ptr[3])
         assert rc in (0, 2), lib.check_message().decode()
-        return rc, dict(zip(("depth", "per", "cap", "general"), out.tolist()))
+        return rc, dict(zip(("depth", "per", "cap", "general", "once", "touched"), out.tolist()))
 
     return run
 
@@ -99,3 +100,31 @@ def test_a_list_that_outgrows_its_room_is_refused(check):
     assert check(s, room=got["per"])[0] == 0
     for room in (got["per"] - 1, got["per"] // 2, 1):
         assert check(s, room=room)[0] == 2
+
+
+def test_the_state_that_a_step_touches(check):
+    """All general: every cell's 13 arrays and six memory variables of each layer it is in (one cell more
+    than npml on every face); all one fluid: 4 arrays and two of them.  The passes stream from 256 MiB on
+    (float elements)."""
+    for shape, npml in (((70, 21, 40), 3), ((64, 64, 64), 0), ((33, 9, 8), 2), ((160, 160, 160), 16), ((152, 152, 152), 16)):
+        nx, ny, nz = shape
+        lay = sum(2 * (npml + 1) * nx * ny * nz // n for n in shape) if npml else 0
+        for solid, arrays, memory in ((1, 13, 6), (0, 4, 2)):
+            got = check(np.full(shape[::-1], solid, np.uint8), npml)[1]
+            want = arrays * nx * ny * nz + memory * lay
+            assert got["touched"] == want // 1000 and got["once"] == int(4 * want > 2 ** 28)
+            off = check(np.full(shape[::-1], solid, np.uint8), npml, fluid=False)[1]
+            assert off["touched"] == (13 * nx * ny * nz + 6 * lay) // 1000
+
+
+@pytest.mark.parametrize("case", range(len(LM.CASES)))
+def test_large_media_take_the_path_they_are_meant_for(check, case):
+    """The media that test_gpu_large.py runs: planes per block, streaming, room, with fluid tiles,
+    fluid sub-tiles and general ones where they are meant to be mixed."""
+    shape, npml, fluid, radius, size, depth, once = LM.CASES[case]
+    solid = LM.clumps(shape, fluid, radius)
+    rc, got = check(solid, npml, nrec=300)
+    assert rc == 0 and got["depth"] == depth
+    assert (got["touched"] * 1000 * size > 2 ** 28) == once
+    assert not fluid or 20 < got["general"] < 980
+    assert got["per"] <= got["cap"]
