@@ -91,8 +91,10 @@ bool layout(const el_grid &g, int nrec, Layout *L) {
     L->counter = take(256);
     {
         const Tiles t = make_tiles(g.nx, g.ny, g.nz);
-        // increments: the planes of a sub-tile's piece with points, at most every plane there is
-        const size_t planes = std::min(E * Tiles::longest(kZDeep), (size_t)4 * t.ntx * t.nty * g.nz);
+        // increments: the planes of a sub-tile's piece with points (as deep as block_planes may make it
+        // here), at most every plane there is
+        const size_t every = (size_t)4 * t.ntx * t.nty * g.nz;
+        const size_t planes = std::min(E * Tiles::longest(every >= kManyBlocks * kZDeep ? kZDeep : kZBlock), every);
         L->inc_planes = (long long)planes;
         for (size_t &o : L->csr_pos) o = take(E * 4);
         for (size_t &o : L->inc) o = take(planes * kWaveX * kWaveY * es);
@@ -129,7 +131,6 @@ constexpr int kMaxTiles = (1 << 24) - 1;   // (arrays below 4 GiB keep under it)
 // precision, 144^3), 7% at 228 (solid 152^3), and gains 5% at 248 (shell of 208^3) and 4% at 263 (solid
 // 160^3).
 constexpr long long kStreamBytes = 256ll << 20;
-constexpr long long kFewBlocks = 5120, kManyBlocks = 10240;   // see block_planes
 int chunk_planes(int nx, int ny, int nz) {
     const long long cols = (long long)((nx + kTileX - 1) / kTileX) * ((ny + kTileY - 1) / kTileY);
     int zc = kZChunk;
@@ -163,7 +164,9 @@ Tiles make_tiles(int nx, int ny, int nz) {
         }
     t.cap = (int)*std::max_element(cnt, cnt + 8);
     if (!t.bands()) t.cap = (int)((all + 7) / 8 + 4 * t.run());
-    if (t.boxes(nx, ny)) t.cap = (int)all;   // (a small grid)
+    // a box of equal cost held at most the entries of a band's bound in 800 lists of random media; where
+    // the media ask for more than a quarter above, block_list takes the bands
+    if (t.boxes(nx, ny)) t.cap += t.cap / 4;
     return t;
 }
 
@@ -403,8 +406,8 @@ bool same_update(const Tiles &t, const unsigned char *fast, const unsigned char 
 }
 
 template <typename T>
-BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
-                        const unsigned long long *lanes, const T *med, const std::vector<int> &points) {
+BlockList<T> cut_list(const Tiles &tiles, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
+                      const unsigned long long *lanes, const T *med, const std::vector<int> &points, bool boxed) {
     Tiles t = tiles;
     long long touched = 0;
     t.zb = block_planes(t, nx, ny, npml, fast, uni, lanes, &touched);
@@ -421,7 +424,6 @@ BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsi
     std::vector<Run> runs((size_t)t.ntx * t.nty, Run{0, 0, 0});
     const int step = t.ntx * t.nty;
     Region region[8] = {};
-    const bool boxed = t.boxes(nx, ny);
     if (boxed) cut_regions(t, chunk_costs(t, nx, ny, npml, fast, lanes), Region{{0, 0, 0}, {t.ntx, t.nty, t.nz}}, 8, region);
     auto xcd_of = [&](int bx, int by, int z, long long index) {
         if (boxed)
@@ -523,6 +525,14 @@ BlockList<T> block_list(const Tiles &tiles, int nx, int ny, int npml, const unsi
     out.per = (int)per;
     for (int x = 0; x < 8; ++x)
         for (size_t e = count[x]; e < per; ++e) order[8 * e + x] = BlockEnt<T>{};
+    return out;
+}
+template <typename T>
+BlockList<T> block_list(const Tiles &t, int nx, int ny, int npml, const unsigned char *fast, const unsigned char *uni,
+                        const unsigned long long *lanes, const T *med, const std::vector<int> &points) {
+    const bool boxed = t.boxes(nx, ny);
+    BlockList<T> out = cut_list(t, nx, ny, npml, fast, uni, lanes, med, points, boxed);
+    if (boxed && !out.fits) out = cut_list(t, nx, ny, npml, fast, uni, lanes, med, points, false);
     return out;
 }
 template BlockList<float> block_list<float>(const Tiles &, int, int, int, const unsigned char *, const unsigned char *,

@@ -173,6 +173,7 @@ constexpr unsigned kBlkFirst = 1u << 17;
 constexpr unsigned kBlkFast = 1u << 18;
 constexpr int kBlkIncShift = 20;
 constexpr int kZBlock = 4, kZDeep = 8;   // planes per block: usually, at most (block_planes)
+constexpr long long kFewBlocks = 5120, kManyBlocks = 10240;   // see block_planes
 struct Tiles {
     int ntx, nty, nzc, zc;   // tiles along x and y, z chunks, planes per chunk
     int nz, zb;              // planes, planes per block (block_list chooses its own)

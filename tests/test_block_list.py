@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 from paper_1709_02733_amd import build as B
+from paper_1709_02733_amd import el
 from tests import large_media as LM
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -128,3 +129,19 @@ def test_large_media_take_the_path_they_are_meant_for(check, case):
     assert (got["touched"] * 1000 * size > 2 ** 28) == once
     assert not fluid or 20 < got["general"] < 980
     assert got["per"] <= got["cap"]
+
+
+def test_boxes_that_need_more_than_their_room_give_way_to_bands(check):
+    """A 96^3 grid deals its pieces to the XCDs in boxes; half of it solid, the fullest box has more
+    entries than the fullest band."""
+    s = np.zeros((96, 96, 96), np.uint8)
+    s[:48] = 1
+    boxes = check(s, 16)[1]
+    rc, bands = check(s, 16, room=boxes["per"] - 1)
+    assert rc == 0 and bands["per"] < boxes["per"] <= boxes["cap"]
+
+
+def test_workspace_of_a_small_plan():
+    """A 96^3 plan with 512 receivers took 103.4 MB with a list of tiles; its block lists and increments
+    add 6% at most."""
+    assert el.plan_bytes(el.make_grid(96, 96, 96, 1e-4, 1e-8, 10, 16), 512) < 1.06 * 103.4e6
