@@ -132,7 +132,8 @@ el_status el_grid_check(const el_grid *grid, const double *rec_xyz, int32_t nrec
 /*
  * Device workspace bytes a plan of this grid and receiver count needs
  * (fields, material maps, C-PML boundary slabs, PML tables, receiver
- * tables, reduction scratch; with relaxation mechanisms the strength map and
+ * tables, block lists and receiver increments with and without the fluid
+ * update, reduction scratch; with relaxation mechanisms the strength map and
  * room for a point list and its memory variables of up to three velocity
  * points per cell).  Host-only; *bytes is written on success.
  */
@@ -313,9 +314,9 @@ el_status el_plan_sizes(el_plan plan, int64_t *ncells, int32_t *nrec, int32_t *n
  * a per-tile table instead of the maps, again with the same results.
  * Inside the other tiles, every column of 1 x 1 cells by the chunk whose
  * cells within two have mu = 0 is marked too and takes the fluid update,
- * storing all three normal stresses: a wavefront (32 x 2 cells of the tile)
- * of such columns runs the fluid loop, and in a wavefront that also holds
- * other columns the fluid lanes run the general loop without the loads they
+ * storing all three normal stresses: a sub-tile (32 x 2 columns of the tile)
+ * of such columns runs the fluid loop, and in a sub-tile that also holds
+ * other columns the fluid lanes run the general loops without the loads they
  * do not need (shear stresses, moduli).
  * A column whose box holds the tile's reference medium (that of its first
  * fluid column) takes it from the table as well.
@@ -351,8 +352,9 @@ el_status el_plan_fluid_path(el_plan plan, int32_t enable, el_fluid_stats *stats
                               /* gathers the previous trace row)               */
 #define EL_K_STRESS       1   /* forward stress pass (+ psi slabs)             */
 #define EL_K_ADJ_VELOCITY 2   /* adjoint pass producing the velocity adjoint   */
+                              /* (it also forms Theta^T of the next trace row) */
 #define EL_K_ADJ_STRESS   3   /* adjoint pass producing the stress adjoint     */
-                              /* (it also scatters the next trace row)         */
+                              /* (it also adds Theta^T of that row)            */
 #define EL_K_GATHER       4   /* receiver gather of the last trace row         */
 #define EL_K_SCATTER      5   /* receiver scatter of the last trace row        */
                               /* (adjoint; the first thing H^T does)           */

@@ -88,8 +88,8 @@ struct Dev {
     __host__ __device__ T *pa(int j, int h) const { return at(coff[j] + 2u * (unsigned)h * cstr[j]); }
     __host__ __device__ T *pb(int j, int h) const { return at(coff[j] + (2u * (unsigned)h + 1u) * cstr[j]); }
     __host__ __device__ T *zab(int h) const { return at(coff[2] + 2u * (unsigned)h * cstr[2]); }
-    // adjoint increments Theta^T y of one trace row: a block of zc x 64 elements (plane, lane) per
-    // sub-tile with scatter points, zero off the points
+    // adjoint increments Theta^T y of one trace row: for every entry of the block list, 64 elements
+    // (lanes) per plane of each of its sub-tiles with scatter points, zero off the points
     __host__ __device__ T *inc() const { return at(incoff); }
     __host__ __device__ int hi(int a) const { return (a == 0 ? nx : (a == 1 ? ny : nz)) - 1 - P; }   // first index of the high slab
     __host__ __device__ int W() const { return P > 0 ? 2 * (P + 7) : 0; }   // slab planes per axis
@@ -107,16 +107,11 @@ struct Dev {
 // overlap (n <= 2P + 9, fewer than ten planes between the layers) one range -2 .. n+1 holds them
 // all at slab coordinates c + 2 (n + 4 < W); d.high is the slab coordinate of cell 0 in the
 // range that a cell near the high layer uses.
-// slab coordinate of a layer cell, -1 outside the layer
-template <typename T>
-__host__ __device__ inline int slab_own(const Dev<T> &d, int a, int c) {
-    return c <= d.P ? c + 2 : (c >= d.hi(a) ? c + d.high[a] : -1);
-}
-// slab coordinate of a cell whose 4-tap stencil along the axis reaches a layer, -1 otherwise
-template <typename T>
-__host__ __device__ inline int slab_near(const Dev<T> &d, int a, int c) {
-    return c <= d.P + 2 ? c + 2 : (c >= d.hi(a) - 2 ? c + d.high[a] : -1);
-}
+// Is a cell in a layer?  Does its 4-tap stencil along the axis reach one?  The slab coordinate of a
+// cell of which either is true.
+__host__ __device__ inline bool in_layer(int c, int P, int hi) { return c <= P || c >= hi; }
+__host__ __device__ inline bool near_layer(int c, int P, int hi) { return c <= P + 2 || c >= hi - 2; }
+__host__ __device__ inline int slab_coord(int c, int P, int high) { return c <= P + 2 ? c + 2 : c + high; }
 // Element order: axis x as [side][k][j][s'] with s' the coordinate within the side's
 // d.xw = P + 7 planes (a tile's rows of one side are contiguous; the two sides are touched by
 // different tiles; a single range is one side of d.xw = W planes), axis y as [k][s][i], axis z

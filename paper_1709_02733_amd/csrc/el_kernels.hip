@@ -357,8 +357,9 @@ __global__ void k_scatter(Dev<T> d, Rec r, const double *y) {
     if (d.P <= 0) return;
     const int crd[3] = {r.ptc[3 * t], r.ptc[3 * t + 1], r.ptc[3 * t + 2]};
     for (int a = 0; a < 3; ++a) {
-        const int s = slab_own(d, a, crd[a]);
-        if (s >= 0) d.mem(a, 3 + a)[slab_byte(d, a, s, crd[0], crd[1], crd[2]) / sizeof(T)] += (a == 2 ? d.zab(0)[2 * crd[2]] : d.pa(a, 0)[crd[a]]) * d.dt * dw;
+        if (!in_layer(crd[a], d.P, d.hi(a))) continue;
+        const int s = slab_coord(crd[a], d.P, d.high[a]);
+        d.mem(a, 3 + a)[slab_byte(d, a, s, crd[0], crd[1], crd[2]) / sizeof(T)] += (a == 2 ? d.zab(0)[2 * crd[2]] : d.pa(a, 0)[crd[a]]) * d.dt * dw;
     }
 }
 

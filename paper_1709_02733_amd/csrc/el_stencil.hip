@@ -275,16 +275,16 @@ struct Slab {
         for (int a = 0; a < 2; ++a) {
             const int c = cell[a], h = d.hi(a);
             const bool on = a == 0 ? onx : ony;
-            own[a] = on && (c <= P || c >= h);
-            near[a] = on && (c <= P + 2 || c >= h - 2);
-            off[a] = slab_byte(d, a, c <= P + 2 ? c + 2 : c + d.high[a], i, j, z0);
+            own[a] = on && in_layer(c, P, h);
+            near[a] = on && near_layer(c, P, h);
+            off[a] = slab_byte(d, a, slab_coord(c, P, d.high[a]), i, j, z0);
         }
         plane(z0);
     }
     __device__ __forceinline__ void plane(int k) {
-        own[2] = k <= P || k >= hiz;
-        near[2] = k <= P + 2 || k >= hiz - 2;
-        sz = k <= P + 2 ? k + 2 : k + highz;
+        own[2] = in_layer(k, P, hiz);
+        near[2] = near_layer(k, P, hiz);
+        sz = slab_coord(k, P, highz);
     }
     __device__ __forceinline__ void next(int k) {
         off[0] += step[0];
