@@ -155,13 +155,12 @@ Tiles make_tiles(int nx, int ny, int nz) {
     // D planes has at most (D + 1) / 3, seven in 18 planes
     const bool deep = t.zc == kZChunk && (long long)t.ntx * t.nty * nz >= kFewBlocks * kZBlock;
     long long cnt[8] = {}, all = 0;
-    for (int by = 0; by < t.nty; ++by)
-        for (int z0 = 0, z1 = 0; z0 < nz; z0 = z1) {
-            for (z1 = z0 + 1; z1 < nz && z1 * 8 / nz == z0 * 8 / nz; ++z1) {}
-            const int n = 4 * t.ntx * (deep ? 7 * (z1 - z0) / 18 + 2 : (z1 - z0 + 1) / 2 + 1);
-            cnt[piece_xcd(t, by, z0, 0)] += n;
-            all += n;
-        }
+    for (int z0 = 0, z1 = 0; z0 < nz; z0 = z1) {
+        for (z1 = z0 + 1; z1 < nz && z1 * 8 / nz == z0 * 8 / nz; ++z1) {}
+        const int n = 4 * t.ntx * (deep ? 7 * (z1 - z0) / 18 + 2 : (z1 - z0 + 1) / 2 + 1);
+        for (int by = 0; by < t.nty; ++by) cnt[piece_xcd(t, by, z0, 0)] += n;
+        all += (long long)n * t.nty;
+    }
     t.cap = (int)*std::max_element(cnt, cnt + 8);
     if (!t.bands()) t.cap = (int)((all + 7) / 8 + 4 * t.run());
     // a box of equal cost held at most the entries of a band's bound in 800 lists of random media; where
@@ -216,27 +215,32 @@ struct Subs {
 };
 Subs subs_of(const Tiles &t, int nx, int ny, const unsigned char *fast, const unsigned long long *lanes, int bx, int by, int q) {
     Subs u;
+    u.in = (nx - bx * kTileX > kWaveX ? 3u : 1u) * (ny - by * kTileY > kWaveY ? 5u : 1u);
+    if (!fast) return u;
+    if (fast[q]) {
+        u.fluid = u.same = u.in;
+        return u;
+    }
+    const unsigned long long *fl = lanes + (size_t)kTileY * q, *un = lanes + (size_t)kTileY * (t.ntiles + (size_t)q);
+    if (!(fl[0] | fl[1] | fl[2] | fl[3])) return u;   // no fluid column: most tiles of a solid
     for (int s = 0; s < 4; ++s) {
+        if (!(u.in >> s & 1u)) continue;
         const int x0 = bx * kTileX + (s & 1) * kWaveX, y0 = by * kTileY + (s >> 1) * kWaveY;
-        if (x0 >= nx || y0 >= ny) continue;
-        u.in |= 1u << s;
-        if (!fast) continue;
+        const unsigned valid = nx - x0 >= kWaveX ? ~0u : (1u << (nx - x0)) - 1;
         bool all = true, same = true;
-        if (!fast[q]) {
-            const unsigned valid = nx - x0 >= kWaveX ? ~0u : (1u << (nx - x0)) - 1;
-            for (int r = 0; r < kWaveY && y0 + r < ny; ++r) {
-                const size_t row = (size_t)kTileY * q + (s >> 1) * kWaveY + r;
-                u.cols[s][r] = (unsigned)(lanes[row] >> ((s & 1) * kWaveX)) & valid;
-                u.uniform[s][r] = (unsigned)(lanes[(size_t)kTileY * t.ntiles + row] >> ((s & 1) * kWaveX)) & valid;
-                all = all && u.cols[s][r] == valid;
-                same = same && u.uniform[s][r] == valid;
-            }
+        for (int r = 0; r < kWaveY && y0 + r < ny; ++r) {
+            const int row = (s >> 1) * kWaveY + r;
+            u.cols[s][r] = (unsigned)(fl[row] >> ((s & 1) * kWaveX)) & valid;
+            u.uniform[s][r] = (unsigned)(un[row] >> ((s & 1) * kWaveX)) & valid;
+            all = all && u.cols[s][r] == valid;
+            same = same && u.uniform[s][r] == valid;
         }
         if (all) u.fluid |= 1u << s;
         if (all && same) u.same |= 1u << s;
     }
     return u;
 }
+static_assert(kTileX == 2 * kWaveX && kTileY == 2 * kWaveY && kTileY == 4, "four sub-tiles of two rows");
 
 // Planes per block.  A long column of planes reads fewer halo planes, a short one gives more
 // wavefronts and a shorter chain of planes per wavefront: kZBlock, two where that leaves few blocks,
@@ -285,7 +289,8 @@ int block_planes(const Tiles &t, int nx, int ny, int P, const unsigned char *fas
                 planes += u.entries() * depth;
                 subs += __builtin_popcount(u.in);
                 general += __builtin_popcount(u.in & ~u.fluid);
-                for (int s = 0; s < 4; ++s)
+                if (!u.fluid) add(bx * kTileX, kTileX, by * kTileY, kTileY, NFIELD + 4, 6);
+                for (int s = 0; u.fluid && s < 4; ++s)
                     if (u.in >> s & 1u) {
                         const bool fl = u.fluid >> s & 1u;
                         add(bx * kTileX + (s & 1) * kWaveX, kWaveX, by * kTileY + (s >> 1) * kWaveY, kWaveY,
