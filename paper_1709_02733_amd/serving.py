@@ -15,8 +15,9 @@ step count and receiver set) arrive as a Poisson stream.  Ways to serve them:
   waits (serve_benchmark's setting), so small requests do not queue behind
   large ones.  Requests leave the group after their last step.
 * executor (run_batched): each admitted request runs on its own slot stream
-  as replays of captured step graphs, concurrently with the others (the
-  steadiest throughput gain over plain).
+  as replays of captured step graphs, concurrently with the others (four 96^3
+  requests 1.2x as fast as one after another; on a mix with grids that fill
+  the device 1-2% below plain).
 * hybrid (run_grouped with an executor): small requests join the group, large
   ones (which fill the device alone) run on executor slots, and the two
   overlap on the device.  The executor keeps two graph replays in flight per
